@@ -15,13 +15,14 @@
 //     In a training step the recording forward has already written these
 //     records (footprint.h; the per-frame figures by frame_reach_kernel)
 //     and this pass is skipped.
-//   pass 2 (tiles): one wavefront owns a 128 x TH tile of the image gradient
-//     in LDS. It walks the segments whose boxes reach the tile (only those
-//     within the per-frame distance can), recomputes their taps, accumulates
-//     weight * g for the taps inside the tile, and stores the finished tile
-//     with plain coalesced stores: no global atomics, no zero fill. The tile
-//     that contains a segment ("home") also computes that segment's motion
-//     gradient, so every pixel's motion gradient is written exactly once.
+//   pass 2 (tiles): one workgroup owns a 128-pixel wide tile of the image
+//     gradient in LDS, as float64. Its wavefronts walk the segments whose boxes
+//     reach the tile (only those within the per-frame distance can), recompute
+//     their taps, add weight * g for the taps inside the tile, and store the
+//     finished tile with plain coalesced stores: no global atomics, no zero
+//     fill. The tile that contains a segment ("home") also computes that
+//     segment's motion gradient, so every pixel's motion gradient is written
+//     exactly once.
 //   pass 3 (far): segments whose box lies more than kFar pixels away are left
 //     to a fallback that scatters with global atomics (frames without such
 //     segments cost one check). For 16-bit storage such frames accumulate in a
@@ -34,7 +35,6 @@
 namespace exw {
 namespace {
 
-constexpr int kTileW = 128;      // width of an image-gradient tile (pass 2)
 constexpr int kThreads = 256;    // four wavefronts
 constexpr int kFarBlocks = 1024; // grid of the fallback and cast passes
 
@@ -51,7 +51,7 @@ struct BwdArgs {
     FrameInfo *info;  // [N]
     int n, c, h, w, k;
     int segs;         // segments per row
-    int tile_h, tiles_x, tiles_y;
+    int tiles_x, tiles_y;
     int frame_32bit;  // C * H * W * sizeof(T) < 2^32: frame-relative 32-bit offsets
     float s[4];
 };
@@ -251,49 +251,29 @@ __device__ __forceinline__ float shift_up1(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
 }
 
-// Channels of one LDS cell: padded to a multiple of four (one 16-byte LDS
-// access per four channels) from three channels up.
-template <int CT>
-struct CellWidth {
-    static constexpr int value = CT <= 2 ? CT : ((CT + 3) / 4) * 4;
+// Tile of the image gradient that one workgroup accumulates in LDS: 128 x H
+// pixels of float64. Taller tiles replay fewer segments (1.8 per segment at
+// 128 x 16, 1.9 at 128 x 12 on pans below a pixel per phase), but the kernel is
+// paid in wavefronts in flight. Four channels, three phases: 80 VGPRs allow 24
+// wavefronts per CU, so three workgroups of 8 must fit the 160 KB of LDS: 12
+// rows (8 x 1080p f32 472 us, f16 439; 16 rows, two workgroups: 506 and 511;
+// 8 rows in 4 wavefronts: 511 and 514). Twelve channels: 6 rows, two
+// workgroups (4 x 1440p bf16 538 us; 4, 5 and 8 rows: 619, 588 and 779); from
+// three phases on, their registers leave room for 4 wavefronts per workgroup
+// (2 x 1440p bf16: three phases, 4 rows 650 us, 6 rows 809, 6 rows in 8
+// wavefronts 888; four phases, 6 rows 1142, 4 rows 1253). One to three channels: three or four workgroups fit as they are (24 or 32 rows
+// for three channels: 353 against 324 us under i.i.d. motion).
+template <int CT, int KT>
+struct TileShape {
+    static constexpr int W = 128;
+    static constexpr int H = CT == 1 ? 32 : (CT <= 3 ? 16 : (CT == 4 ? 12 : (KT == 3 ? 4 : 6)));
+    static constexpr int waves = CT == 12 && KT >= 3 ? 4 : 8;
+    static constexpr int cells = W * H;
+    // Candidate segments: rows within kFar of the tile, at most 8 columns.
+    static constexpr int max_cand = (H + 2 * kFar) * 8;
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-template <int CP>
-__device__ __forceinline__ void cell_read(const float *acc, int cell, float (&v)[CP]) {
-    if constexpr (CP % 4 == 0) {
-#pragma unroll
-        for (int q = 0; q < CP / 4; ++q) {
-            const f32x4 t = reinterpret_cast<const f32x4 *>(acc)[cell * (CP / 4) + q];
-            v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-        }
-    } else if constexpr (CP == 2) {
-        const f32x2 t = reinterpret_cast<const f32x2 *>(acc)[cell];
-        v[0] = t.x; v[1] = t.y;
-    } else {
-        v[0] = acc[cell];
-    }
-}
-
-template <int CP>
-__device__ __forceinline__ void cell_write(float *acc, int cell, const float (&v)[CP]) {
-    if constexpr (CP % 4 == 0) {
-#pragma unroll
-        for (int q = 0; q < CP / 4; ++q) {
-            f32x4 t;
-            t.x = v[4 * q]; t.y = v[4 * q + 1]; t.z = v[4 * q + 2]; t.w = v[4 * q + 3];
-            reinterpret_cast<f32x4 *>(acc)[cell * (CP / 4) + q] = t;
-        }
-    } else if constexpr (CP == 2) {
-        f32x2 t;
-        t.x = v[0]; t.y = v[1];
-        reinterpret_cast<f32x2 *>(acc)[cell] = t;
-    } else {
-        acc[cell] = v[0];
-    }
-}
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // What one replayed segment needs from global memory, loaded one segment
 // ahead of its use.
@@ -304,52 +284,61 @@ struct SegLoad {
     T g[KT][CT];
 };
 
-// One wavefront owns a kTileW x TH tile of the image gradient and keeps it in
-// LDS as cells of CP consecutive channels. No other wavefront touches that
-// LDS, so no barriers are needed.
+// One workgroup owns a 128 x H tile of the image gradient and accumulates it in
+// LDS, in float64: on this hardware a float32 LDS addition takes 3 cycles per
+// active lane (193 cycles per wavefront), a float64 one 9 cycles per wavefront
+// (16-23 with scattered lanes) whatever the lanes' addresses, so every
+// wavefront of the workgroup may add to every cell, lanes that share a cell
+// need no turns, and a segment that reaches the tile is replayed by one
+// wavefront only. (Before: one wavefront per 128 x 3 tile with float32 cells,
+// 2.8 replays per segment and turns for lanes that share a cell; 8 x 1080p
+// RGBA three phases f32 611 -> 472 us, f16 498 -> 439, 4 x 4K f16 841 -> 760,
+// 4 x 1440p 12-channel bf16 675 -> 538; under i.i.d. motion 8 x 1080p RGB one
+// phase 634 -> 324, RGBA three phases 3470 -> 690; a zooming camera, RGBA three
+// phases 712 -> 456.) The sums of a cell land in any order; rounded from
+// float64, they differ from run to run only where two orders straddle a
+// float32 rounding boundary.
 //
 // Work list: the segments whose boxes reach the tile (only rows and columns
 // within the per-frame reach can), plus the tile's own segments ("home"),
 // which are replayed even when their taps lie elsewhere because the home tile
-// computes their motion gradient. Candidates are classified 64 at a time from
-// their boxes; motion, upstream-gradient and tap-offset loads run one segment
-// ahead.
+// computes their motion gradient. The wavefronts classify the candidates 64 at
+// a time from their boxes into a list in LDS and replay it in turn; motion,
+// upstream-gradient and tap-offset loads run one segment ahead.
 //
-// Accumulation: for one segment and phase, the lanes whose integer tap offset
-// (x - x0, y - y0) equals that of the first lane with an in-tile tap
-// ("uniform" lanes) hit pairwise distinct cells, and lane j's right-hand taps
-// land on lane j+1's left-hand cells. Each lane therefore adds, without
-// atomics, its own left taps plus its left neighbour's right taps to its cell
-// of the uniform pattern (one read-add-write of the whole cell per row); lane
-// 63 also adds its right taps one cell further. The pattern's row is the same
-// for every lane, so a row outside the tile is skipped by the whole wavefront;
-// lanes whose column lies outside the tile read a cell but do not write it.
-// Lanes with another offset (motion boundaries, random motion) add their taps
-// one at a time: where a cell has a spare word (three channels in four) by
-// whole-cell read-add-writes that colliding lanes take in turns, otherwise by
-// LDS atomics, one per channel, which serialise per lane on this hardware;
-// the uniform path must carry the bulk of the work.
+// Uniform segments (pass 1 found every lane valid with one offset per phase):
+// lane j's right-hand taps land on lane j+1's left-hand cells, so each lane
+// adds its own left taps plus its left neighbour's right taps in one addition
+// per row and channel, and lane 63 its right taps one cell further; the
+// samples of their motion gradient are aligned loads shared by the phases
+// whose offsets agree. Other segments add each lane's four taps.
 //
-// Uniform segments (pass 1 found every lane valid with one offset per phase)
-// skip the per-lane split, the pattern search and the atomics, and gather the
-// samples of their motion gradient with aligned loads shared by the phases
-// whose offsets agree. The vector-memory pipeline, not the ALUs, bounds this
-// kernel on the pan-and-rectangle workloads, so load instructions are what
-// these paths save.
+// What bounds it: the vector ALU issues 55-60 % of the cycles and the LDS
+// additions 65 %, and neither covers the other at six wavefronts per SIMD;
+// HBM traffic is 1.2x the algorithmic bytes (2.1x before). Measured and left
+// out: lane 63's taps gathered into one addition (DPP moves cost more than
+// the additions they save: +6 %), every tap added by its own lane (+6 %), the
+// lower tap row carried in registers to the next segment (no gain), samples of
+// all phases loaded before the scatter (no gain), gathering by offset class
+// into registers (a strip of 128 x 8 pixels per wavefront: 640 us, since the
+// motion and samples re-read per phase miss the L2).
 template <typename T, int CT, int KT>
-__global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
-    extern __shared__ __attribute__((aligned(16))) float acc[];  // [TH * kTileW][CP]
-    constexpr int CP = CellWidth<CT>::value;
-    const int TH = a.tile_h;
+__global__ __launch_bounds__((TileShape<CT, KT>::waves * kSegW)) void adjoint_tiles_kernel(BwdArgs<T> a) {
+    using Tile = TileShape<CT, KT>;
+    constexpr int TW = Tile::W, TH = Tile::H, NW = Tile::waves;
+    __shared__ __attribute__((aligned(16))) double acc[CT * Tile::cells];  // [CT][TH][TW]
+    __shared__ uint16_t list[Tile::max_cand];
+    __shared__ int list_len;
     const int w = a.w, h = a.h;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x % kSegW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kSegW);
 
     const int b = xcd_tile_index(blockIdx.x, gridDim.x);
     const int tx = b % a.tiles_x;
     const int rest = b / a.tiles_x;
     const int ty = rest % a.tiles_y;
     const int in = rest / a.tiles_y;
-    const int tx0 = tx * kTileW, ty0 = ty * TH;
+    const int tx0 = tx * TW, ty0 = ty * TH;
     const int64_t hw = static_cast<int64_t>(h) * w;
     const T *img = a.src ? a.src + static_cast<int64_t>(in) * CT * hw : nullptr;
     const float *mu = a.mv + (2 * static_cast<int64_t>(in)) * hw;
@@ -357,10 +346,6 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
     const T *gframe = a.gout + static_cast<int64_t>(in) * KT * CT * hw;
     const FrameInfo fi = a.info[in];
     const int reach = min(fi.reach, kFar);
-    const int ncells = TH * kTileW;
-
-    for (int i = lane; i < ncells * CP / 4; i += kSegW)
-        reinterpret_cast<f32x4 *>(acc)[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     // Candidate segments: rows within `reach` of the tile, and columns whose
     // 64-pixel span lies within `reach` of it; the home segments are among them.
@@ -368,7 +353,7 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
     const int r_hi = min(h - 1, ty0 + TH - 1 + reach);
     const int ca = tx0 - (kSegW - 1) - reach;
     const int sc_lo = ca > 0 ? (ca + kSegW - 1) / kSegW : 0;
-    const int sc_hi = min(a.segs - 1, (tx0 + kTileW - 1 + reach) / kSegW);
+    const int sc_hi = min(a.segs - 1, (tx0 + TW - 1 + reach) / kSegW);
     // Candidate i is row r_lo + (i >> sh), column sc_lo + (i & cm): the columns
     // are padded to a power of two (at most 8 of them) so that no division is
     // needed; padding columns are never hits.
@@ -387,30 +372,37 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
     auto classify = [&](const Box &bx, int i) -> int {
         if (i >= total || (i & cm) >= nsc) return 0;
         const int r = r_lo + (i >> sh), sc = sc_lo + (i & cm);
-        const bool home = a.gmv && (unsigned)(r - ty0) < (unsigned)TH && sc * kSegW / kTileW == tx;
+        const bool home = a.gmv && (unsigned)(r - ty0) < (unsigned)TH && sc * kSegW / TW == tx;
         const bool near = bx.x_lo <= bx.x_hi && box_reach(bx, sc * kSegW, r) <= kFar &&
-                          bx.x_hi >= tx0 && bx.x_lo < tx0 + kTileW && bx.y_hi >= ty0 &&
+                          bx.x_hi >= tx0 && bx.x_lo < tx0 + TW && bx.y_hi >= ty0 &&
                           bx.y_lo < ty0 + TH;
         return (near ? 1 : 0) | (home ? 2 : 0);
     };
 
-    int base = 0;
-    unsigned long long m_hit = 0, m_near = 0;
-    // Next segment to replay as (candidate << 1) | near, or -1 when done. A
-    // batch's boxes are loaded when it is classified: holding the next batch's
-    // boxes through the replays would cost four registers per lane all along.
-    auto next_seg = [&]() -> int {
-        while (m_hit == 0) {
-            if (base >= total) return -1;
-            const int cls = classify(box_of(base + lane), base + lane);
-            m_hit = __ballot(cls != 0);
-            m_near = __ballot(cls & 1);
-            base += kSegW;
-        }
-        const int j = __builtin_ctzll(m_hit);
-        m_hit &= m_hit - 1;
-        return ((base - kSegW + j) << 1) | static_cast<int>((m_near >> j) & 1ull);
-    };
+    // (the first boxes are on their way while the tile is cleared)
+    Box bx = box_of(wave * kSegW + lane);
+    if (threadIdx.x == 0) list_len = 0;
+    for (int i = threadIdx.x; i < CT * Tile::cells / 2; i += NW * kSegW)
+        reinterpret_cast<f64x2 *>(acc)[i] = f64x2{0.0, 0.0};
+    __syncthreads();
+
+    // The segments to replay, listed by all wavefronts together as
+    // (candidate << 1) | near (in no particular order).
+    for (int base = wave * kSegW; base < total; base += NW * kSegW) {
+        const int i = base + lane;
+        const int cls = classify(bx, i);
+        if (base + NW * kSegW < total) bx = box_of(i + NW * kSegW);
+        const unsigned long long m = __ballot(cls != 0);
+        int pos = 0;
+        if (lane == 0 && m) pos = atomicAdd(&list_len, static_cast<int>(__popcll(m)));
+        pos = __builtin_amdgcn_readfirstlane(pos);
+        if (cls != 0)
+            list[pos + __popcll(m & ((1ull << lane) - 1ull))] =
+                static_cast<uint16_t>((i << 1) | (cls & 1));
+    }
+    __syncthreads();
+    const int n_seg = list_len;
+
     // Plane base pointers, loop-invariant and wave-uniform (scalar registers);
     // each load adds a 32-bit in-plane offset.
     const T *gplane[KT][CT];
@@ -441,41 +433,41 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
             for (int ch = 0; ch < CT; ++ch) d.g[k][ch] = *at(gplane[k][ch], pc);
     };
 
-    // Uniform-pattern accumulation of one phase: lane j adds its left taps and
-    // lane j-1's right taps to pattern cell (row uy0 / uy0 + 1, column ux);
+    auto add_cell = [&](int cell, int ch, float v) {
+        __hip_atomic_fetch_add(acc + ch * Tile::cells + cell, static_cast<double>(v),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    // Accumulation of one phase of a uniform segment: lane j adds its left
+    // taps plus lane j-1's right taps to column ux of rows uy0 and uy0 + 1;
     // uy0 is wave-uniform, ux = ux(lane 0) + lane.
-    auto scatter_pattern = [&](int ux, int uy0, float fx, float fy, const float (&gg)[CT]) {
+    auto scatter_uniform = [&](int ux, int uy0, float fx, float fy, const float (&gg)[CT]) {
         const float w00 = (1.0f - fx) * (1.0f - fy), w01 = fx * (1.0f - fy);
         const float w10 = (1.0f - fx) * fy, w11 = fx * fy;
-        // Lanes whose column lies outside the tile read some cell of the row
-        // but do not write it back (the lane shift in the sums below needs
-        // every lane active).
-        const bool cx = (unsigned)ux < (unsigned)kTileW;
-        const int col = cx ? ux : 0;
+        const bool cx = (unsigned)ux < (unsigned)TW;
+        const bool ex = lane == kSegW - 1 && (unsigned)(ux + 1) < (unsigned)TW;
         auto add_row = [&](int r, float wl, float wr) {
-            const int cell = r * kTileW + col;
-            float c[CP], right[CT];
-            cell_read<CP>(acc, cell, c);
+            const int cell = r * TW + ux;
+            float v[CT], right[CT];
 #pragma unroll
             for (int ch = 0; ch < CT; ++ch) {
                 right[ch] = wr * gg[ch];
-                c[ch] = fmaf(wl, gg[ch], c[ch]) + shift_up1(right[ch]);
+                v[ch] = fmaf(wl, gg[ch], shift_up1(right[ch]));
             }
-            if (cx) cell_write<CP>(acc, cell, c);
-            // lane 63's right-hand taps, one cell to the right
-            if (lane == kSegW - 1 && (unsigned)(ux + 1) < (unsigned)kTileW) {
-                const int c1 = r * kTileW + ux + 1;
-                cell_read<CP>(acc, c1, c);
+            if (cx) {
 #pragma unroll
-                for (int ch = 0; ch < CT; ++ch) c[ch] += right[ch];
-                cell_write<CP>(acc, c1, c);
+                for (int ch = 0; ch < CT; ++ch) add_cell(cell, ch, v[ch]);
+            }
+            // lane 63's right-hand taps, one cell to the right
+            if (ex) {
+#pragma unroll
+                for (int ch = 0; ch < CT; ++ch) add_cell(cell + 1, ch, right[ch]);
             }
         };
         if ((unsigned)uy0 < (unsigned)TH) add_row(uy0, w00, w01);
         if ((unsigned)(uy0 + 1) < (unsigned)TH) add_row(uy0 + 1, w10, w11);
     };
 
-    // Replay of one segment (code from next_seg, loads from load_seg).
+    // Replay of one segment (code from the list, loads from load_seg).
     auto process = [&](const int code, const SegLoad<T, CT, KT> &cur) {
         const int i = code >> 1;  // wave-uniform
         const bool near = code & 1;
@@ -516,7 +508,7 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
         }
 
         // Motion gradient of the home segments (every pixel written once).
-        if (a.gmv && (unsigned)(y - ty0) < (unsigned)TH && sx0 / kTileW == tx) {
+        if (a.gmv && (unsigned)(y - ty0) < (unsigned)TH && sx0 / TW == tx) {
             float gu = 0.0f, gv = 0.0f;
             if (seg_uniform && a.frame_32bit) {
                 // The taps of a uniform segment are contiguous across lanes,
@@ -545,17 +537,25 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
                     a1 = to_f32(*at(img, r1 + xa));
                     b1 = to_f32(*at(img, r1 + xb));
                 };
-                // per-phase sums over channels, in channel order as in
-                // motion_grad_phase
-                float su[KT], sv[KT];
+                // Per phase, sums over the channels of g times the sample
+                // differences (upper and lower row along x, left and right
+                // column along y); the fractions are applied to the sums, as
+                // soon as a phase's are complete (kept for all phases they
+                // cost 12 registers: 8 x 1080p f32 472 -> 499 us).
+                float su[KT], sv[KT], s0[KT], s1[KT], s2[KT], s3[KT];
 #pragma unroll
-                for (int k = 0; k < KT; ++k) su[k] = sv[k] = 0.0f;
+                for (int k = 0; k < KT; ++k)
+                    su[k] = sv[k] = s0[k] = s1[k] = s2[k] = s3[k] = 0.0f;
                 auto accumulate = [&](int k, int ch, float a0, float b0, float a1, float b1) {
                     const float fx = t[k].ax.f, fy = t[k].ay.f;
-                    const float dsx = fmaf(fy, b1 - a1, (1.0f - fy) * (b0 - a0));
-                    const float dsy = fmaf(fx, b1 - b0, (1.0f - fx) * (a1 - a0));
-                    su[k] = fmaf(g[k][ch], dsx, su[k]);
-                    sv[k] = fmaf(g[k][ch], dsy, sv[k]);
+                    s0[k] = fmaf(g[k][ch], b0 - a0, s0[k]);
+                    s1[k] = fmaf(g[k][ch], b1 - a1, s1[k]);
+                    s2[k] = fmaf(g[k][ch], a1 - a0, s2[k]);
+                    s3[k] = fmaf(g[k][ch], b1 - b0, s3[k]);
+                    if (ch == CT - 1) {
+                        su[k] = fmaf(fy, s1[k], (1.0f - fy) * s0[k]);
+                        sv[k] = fmaf(fx, s3[k], (1.0f - fx) * s2[k]);
+                    }
                 };
                 if (same) {  // wave-uniform
                     // Lane j's right taps are lane j+1's left taps (a DPP
@@ -626,8 +626,8 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
                 // pattern column of lane 0 and pattern row (wave-uniform); the
                 // taps span columns ux0 .. ux0 + 64 and rows uy0, uy0 + 1
                 const int ux0 = sx0 - ox[k] - tx0, uy0 = y - oy[k] - ty0;
-                if (ux0 < -kSegW || ux0 >= kTileW || uy0 < -1 || uy0 >= TH) continue;
-                scatter_pattern(ux0 + lane, uy0, t[k].ax.f, t[k].ay.f, g[k]);
+                if (ux0 < -kSegW || ux0 >= TW || uy0 < -1 || uy0 >= TH) continue;
+                scatter_uniform(ux0 + lane, uy0, t[k].ax.f, t[k].ay.f, g[k]);
             }
             return;
         }
@@ -637,122 +637,64 @@ __global__ __launch_bounds__(kSegW) void adjoint_tiles_kernel(BwdArgs<T> a) {
             // (row) before it: the second is the first + 1, or the same at the
             // last column (row).
             const int lx0 = t[k].ax.i0 - tx0, ly0 = t[k].ay.i0 - ty0;
-            const bool any = t[k].valid && (unsigned)(lx0 + 1) < (unsigned)(kTileW + 1) &&
-                             (unsigned)(ly0 + 1) < (unsigned)(TH + 1);
-            const unsigned long long any_m = __ballot(any);
-            if (any_m == 0ull) continue;  // wave-uniform
-            // Uniform offset: that of the first lane with an in-tile tap.
-            const int offx = x - t[k].ax.i0, offy = y - t[k].ay.i0;
-            const int src_lane = __builtin_ctzll(any_m);
-            const int rx = __builtin_amdgcn_readlane(offx, src_lane);
-            const int ry = __builtin_amdgcn_readlane(offy, src_lane);
-            const bool uni = any && offx == rx && offy == ry;
-            // (lanes off the pattern take part with g = 0: their cell of the
-            // pattern still receives the left neighbour's taps)
-            float gg[CT];
-#pragma unroll
-            for (int ch = 0; ch < CT; ++ch) gg[ch] = uni ? g[k][ch] : 0.0f;
+            if (!(t[k].valid && (unsigned)(lx0 + 1) < (unsigned)(TW + 1) &&
+                  (unsigned)(ly0 + 1) < (unsigned)(TH + 1)))
+                continue;
             const float fx = t[k].ax.f, fy = t[k].ay.f;
-            scatter_pattern(x - rx - tx0, y - ry - ty0, fx, fy, gg);
-            // Lanes off the uniform pattern (motion boundaries, random motion).
-            if constexpr (CP > CT) {
-                // Cells have a spare word: whole-cell read-add-writes, one tap
-                // position at a time. Lanes whose cells coincide take turns:
-                // each writes its lane number into the cell's spare word and
-                // the lane that reads its own number back adds its tap this
-                // round (LDS accesses of one wavefront complete in order; every
-                // round retires at least one lane per contested cell). One
-                // read-add-write covers all channels, where atomics take one
-                // per channel, and the order of the additions is fixed.
-                const bool off = any && !uni;
-                if (__ballot(off)) {
-                    const float w00 = (1.0f - fx) * (1.0f - fy), w01 = fx * (1.0f - fy);
-                    const float w10 = (1.0f - fx) * fy, w11 = fx * fy;
-                    const int lx1 = t[k].ax.i1 - tx0, ly1 = t[k].ay.i1 - ty0;
+            const int lx1 = t[k].ax.i1 - tx0, ly1 = t[k].ay.i1 - ty0;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int lx = (q & 1) ? lx1 : lx0, ly = (q & 2) ? ly1 : ly0;
-                        const float wq = q == 0 ? w00 : (q == 1 ? w01 : (q == 2 ? w10 : w11));
-                        bool pend = off && (unsigned)lx < (unsigned)kTileW &&
-                                    (unsigned)ly < (unsigned)TH && wq != 0.0f;
-                        const int cell = pend ? ly * kTileW + lx : 0;
-                        // (atomic accesses: the read must not be served from
-                        // this lane's own store)
-                        int *own = reinterpret_cast<int *>(acc) + cell * CP + (CP - 1);
-                        while (__ballot(pend)) {  // wave-uniform
-                            if (pend)
-                                __hip_atomic_store(own, lane, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-                            if (pend && __hip_atomic_load(own, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_WORKGROUP) == lane) {
-                                float c[CP];
-                                cell_read<CP>(acc, cell, c);
+            for (int q = 0; q < 4; ++q) {
+                const int lx = (q & 1) ? lx1 : lx0, ly = (q & 2) ? ly1 : ly0;
+                const float wq = ((q & 1) ? fx : 1.0f - fx) * ((q & 2) ? fy : 1.0f - fy);
+                if ((unsigned)lx < (unsigned)TW && (unsigned)ly < (unsigned)TH && wq != 0.0f) {
 #pragma unroll
-                                for (int ch = 0; ch < CT; ++ch) c[ch] = fmaf(wq, g[k][ch], c[ch]);
-                                cell_write<CP>(acc, cell, c);
-                                pend = false;
-                            }
-                        }
-                    }
-                }
-            } else if (__ballot(any && !uni)) {  // LDS atomics
-                if (any && !uni) {
-                    const float w00 = (1.0f - fx) * (1.0f - fy), w01 = fx * (1.0f - fy);
-                    const float w10 = (1.0f - fx) * fy, w11 = fx * fy;
-                    const int lx1 = t[k].ax.i1 - tx0, ly1 = t[k].ay.i1 - ty0;
-                    const bool inx0 = (unsigned)lx0 < (unsigned)kTileW;
-                    const bool inx1 = (unsigned)lx1 < (unsigned)kTileW;
-                    const bool iny0 = (unsigned)ly0 < (unsigned)TH;
-                    const bool iny1 = (unsigned)ly1 < (unsigned)TH;
-#pragma unroll
-                    for (int ch = 0; ch < CT; ++ch) {
-                        const float gk = g[k][ch];
-                        if (inx0 && iny0 && w00 != 0.0f)
-                            atomicAdd(acc + (ly0 * kTileW + lx0) * CP + ch, w00 * gk);
-                        if (inx1 && iny0 && w01 != 0.0f)
-                            atomicAdd(acc + (ly0 * kTileW + lx1) * CP + ch, w01 * gk);
-                        if (inx0 && iny1 && w10 != 0.0f)
-                            atomicAdd(acc + (ly1 * kTileW + lx0) * CP + ch, w10 * gk);
-                        if (inx1 && iny1 && w11 != 0.0f)
-                            atomicAdd(acc + (ly1 * kTileW + lx1) * CP + ch, w11 * gk);
-                    }
+                    for (int ch = 0; ch < CT; ++ch)
+                        add_cell(ly * TW + lx, ch, wq * g[k][ch]);
                 }
             }
         }
     };
 
-    // The next segment's loads are in flight while the current one is
-    // replayed. (Alternating two buffers without the copy needs more
+    // Wavefront i replays segments i, i + NW, ... of the list. The next
+    // segment's loads are in flight while the current one is replayed. (Alternating two buffers without the copy needs more
     // registers and was measured slower for 16-bit frames.)
     SegLoad<T, CT, KT> cur, nxt;
-    int code = next_seg();
-    if (code >= 0) load_seg(code, cur);
+    int j = wave;
+    int code = -1;
+    if (j < n_seg) {
+        code = __builtin_amdgcn_readfirstlane(list[j]);
+        load_seg(code, cur);
+    }
     while (code >= 0) {
-        const int ncode = next_seg();
-        if (ncode >= 0) load_seg(ncode, nxt);
+        j += NW;
+        int ncode = -1;
+        if (j < n_seg) {
+            ncode = __builtin_amdgcn_readfirstlane(list[j]);
+            load_seg(ncode, nxt);
+        }
         process(code, cur);
         code = ncode;
         cur = nxt;
     }
+    __syncthreads();
 
     if (!a.gsrc) return;
     // Store the finished tile, one pixel (all channels) per lane and step. 16-bit
     // frames that also receive far-segment atomics go through the float32
     // accumulator instead.
     const bool to_accum = fi.has_far && a.accum32 != nullptr;
-    for (int c = lane; c < ncells; c += kSegW) {
-        const int X = tx0 + c % kTileW, Y = ty0 + c / kTileW;
+    for (int c = threadIdx.x; c < Tile::cells; c += NW * kSegW) {
+        const int X = tx0 + c % TW, Y = ty0 + c / TW;
         if (X >= w || Y >= h) continue;
-        float v[CP];
-        cell_read<CP>(acc, c, v);
         const uint32_t o = static_cast<uint32_t>(Y) * static_cast<uint32_t>(w) + X;
         const int64_t frame = static_cast<int64_t>(in) * CT * hw;
 #pragma unroll
         for (int ch = 0; ch < CT; ++ch) {
+            const float v = static_cast<float>(acc[ch * Tile::cells + c]);
             if (to_accum)
-                *at(a.accum32 + frame + ch * hw, o) = v[ch];
+                *at(a.accum32 + frame + ch * hw, o) = v;
             else
-                *at(a.gsrc + frame + ch * hw, o) = from_f32<T>(v[ch]);
+                *at(a.gsrc + frame + ch * hw, o) = from_f32<T>(v);
         }
     }
 }
@@ -988,17 +930,6 @@ hipError_t footprint_pass(const float *mv, Box *boxes, SegOffsets *offs, FrameIn
     return hipGetLastError();
 }
 
-int tile_rows_for(int c) {
-    // One wavefront per 128 x TH tile of float32 accumulators (2 KB per
-    // four-channel row). Taller tiles replay fewer segments (3.5 replays per
-    // segment at TH = 2, 2.9 at TH = 3, 2.5 at TH = 4 on workload 2) but hold
-    // more LDS per wavefront; measured on workload 2, TH = 3 is fastest for
-    // float32 and 16-bit frames with up to four channels (TH = 2 and TH = 4
-    // were slower in both), and on three-channel frames under i.i.d. motion
-    // (8 x 1080p: 634-649 us against 780, 676 and 774 at TH = 2, 4, 6).
-    return c <= 4 ? 3 : 2;
-}
-
 template <typename T, int CT, int KT>
 hipError_t run(BwdArgs<T> a, const BwdWorkspace &ws, hipStream_t st) {
     const int64_t segs_total = static_cast<int64_t>(a.n) * a.h * a.segs;
@@ -1014,10 +945,12 @@ hipError_t run(BwdArgs<T> a, const BwdWorkspace &ws, hipStream_t st) {
         (e = footprint_pass<KT>(a.mv, a.boxes, a.offs, a.info, a.n, a.h, a.w, a.s, st)) != hipSuccess)
         return e;
 
-    const size_t lds = sizeof(float) * CellWidth<CT>::value * a.tile_h * kTileW;
+    using Tile = TileShape<CT, KT>;
+    a.tiles_x = (a.w + Tile::W - 1) / Tile::W;
+    a.tiles_y = (a.h + Tile::H - 1) / Tile::H;
     const int64_t tiles = static_cast<int64_t>(a.n) * a.tiles_x * a.tiles_y;
     hipLaunchKernelGGL((adjoint_tiles_kernel<T, CT, KT>), dim3(static_cast<unsigned>(tiles)),
-                       dim3(kSegW), lds, st, a);
+                       dim3(Tile::waves * kSegW), 0, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
 
     float *far_accum = ws.accum32 ? ws.accum32 : reinterpret_cast<float *>(a.gsrc);
@@ -1059,9 +992,6 @@ hipError_t run_typed(const void *src, const float *mv, const WarpShape &s, const
     a.info = reinterpret_cast<FrameInfo *>(ws.info);
     a.n = s.n; a.c = s.c; a.h = s.h; a.w = s.w; a.k = s.k;
     a.segs = (s.w + kSegW - 1) / kSegW;
-    a.tile_h = tile_rows_for(s.c);
-    a.tiles_x = (s.w + kTileW - 1) / kTileW;
-    a.tiles_y = (s.h + a.tile_h - 1) / a.tile_h;
     a.frame_32bit = static_cast<uint64_t>(s.c) * s.h * s.w * sizeof(T) < (uint64_t(1) << 32);
     for (int j = 0; j < 4; ++j) a.s[j] = s.phases[j];
     switch (s.c) {

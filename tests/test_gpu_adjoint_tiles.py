@@ -1,0 +1,59 @@
+"""Adjoint tiles at their edges: frames one row or column short of, equal to
+and past a tile, for every tile shape, under motion that mixes rigid, random
+and converging parts (many pixels onto one cell), against the float64 oracle."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2307_12607_amd as exw
+from oracle import warp_oracle
+from gpu_util import announce, half_ulp, need_gpu, stored, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+# (channels, phases, tile rows): one entry per tile shape of the kernel
+SHAPES = [(1, 1, 32), (2, 3, 16), (3, 1, 16), (3, 3, 16), (4, 3, 12), (4, 4, 12), (12, 1, 6),
+          (12, 3, 4), (12, 4, 6)]
+PHASES = [0.25, 0.5, 0.75, 1.0]
+
+
+def mixed_motion(rng, h, w):
+    """Rigid top, random middle, bottom rows that all sample one pixel."""
+    mv = np.empty((1, 2, h, w), np.float32)
+    mv[:, 0], mv[:, 1] = 2.75, -1.5
+    a, b = h // 3, 2 * h // 3
+    mv[:, :, a:b] = rng.uniform(-5, 5, size=(1, 2, b - a, w))
+    x = np.arange(w, dtype=np.float32)
+    mv[:, 0, b:] = x - np.float32(min(w - 1, 70) - 0.375)
+    mv[:, 1, b:] = 0.25
+    return mv
+
+
+@pytest.mark.parametrize("c,k,rows", SHAPES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tile_edges(c, k, rows, dtype):
+    dev = need_gpu()
+    phases = [1.0] if k == 1 else PHASES[:k]
+    rng = np.random.default_rng(100 * c + k)
+    for h, w in ((rows - 1, 127), (rows, 128), (rows + 1, 129), (2 * rows + 1, 191), (3, 2)):
+        announce("tiles", c, k, h, w, dtype)
+        src = rng.random((1, c, h, w), dtype=np.float32)
+        mv = mixed_motion(rng, h, w)
+        g = rng.standard_normal((1, k, c, h, w)).astype(np.float32)
+        src_q, g_q = stored(src, dtype), stored(g, dtype)
+        ref_gs, ref_gm = warp_oracle.backward(src_q, mv, phases, g_q)
+        # sums of |weight * g|, and of the motion gradient's terms: float32
+        # products round by 2^-24 each, a few per term, so 2^-19 of the sum of
+        # magnitudes (at least of 1) bounds them
+        abs_gs, _ = warp_oracle.backward(src_q, mv, phases, np.abs(g_q))
+        abs_gm = np.abs(g_q).sum(axis=(1, 2))[:, None]
+        gs, gm = exw.warp_backward(to_dev(src, dtype, dev), torch.from_numpy(mv).to(dev), phases,
+                                   to_dev(g, dtype, dev))
+        torch.cuda.synchronize()
+        tol = 2.0 ** -19
+        bound = tol * np.maximum(1.0, abs_gs)
+        if dtype != "f32":
+            bound = bound + half_ulp(ref_gs, dtype)
+        assert (np.abs(to_host(gs) - ref_gs) <= bound).all(), (h, w)
+        assert (np.abs(to_host(gm) - ref_gm) <= tol * np.maximum(1.0, abs_gm)).all(), (h, w)
