@@ -6,17 +6,25 @@
 // SSIM is the Gaussian-window index (11 x 11 window, standard deviation 1.5,
 // C1 = (0.01 peak)^2, C2 = (0.03 peak)^2) evaluated where the window lies
 // inside the frame and averaged over those positions and the channels. The
-// window is separable, so one wavefront owns a strip of 64 output columns x
-// kStripRows output rows of one channel: each input row of the strip (plus
-// the 10-pixel halo) is staged once in LDS, filtered horizontally in
-// registers (window sums of x, y, x^2, y^2, xy), and added into the eleven
-// output rows it contributes to, which live in registers as a ring indexed
-// at compile time (the row loop is unrolled by 11). All filtering is float64:
-// on this hardware float64 FMAs issue at the same rate as unpacked float32
-// ones, and the local variances E[x^2] - E[x]^2 would otherwise lose their
-// low digits. The squared differences for the MSE are summed in the same
-// pass over each input pixel the strip owns. Partials are folded per frame
-// in a fixed order, so the results are reproducible bit for bit.
+// index needs four window sums: of x, y, x^2 + y^2 (only the sum of the two
+// variances enters) and x y. The window is separable. A workgroup of NW
+// wavefronts owns a strip of 64 NW input columns of one channel, a column per
+// lane, and walks down its rows: each row's four values are added into the
+// eleven output rows they feed, held in float64 registers as a ring of twelve
+// slots (indexed at compile time: batches of four rows, unrolled by three).
+// Four finished rows at a time go through LDS, where each lane takes four
+// adjacent output columns of one row: 14 columns are read for 4 outputs, so
+// LDS moves 14 / 4 values per output and sum instead of 11. The squared errors
+// for the MSE are summed on the way. Partials are folded per frame in a fixed
+// order, so the results are reproducible bit for bit.
+//
+// Bound: the float64 vector ALU, which issues at the rate of unpacked float32
+// (float32 sums would lose the low digits of E[x^2] - E[x]^2). Operations per
+// output: 44 fused multiply-adds vertically, 44 horizontally, ~12 to form the
+// four values and convert, ~30 for the index. Filtering horizontally first,
+// each lane its own column from LDS (22 reads, 22 conversions, 7 operations per
+// tap for five sums) took ~190 and 15 % more for the halo rows:
+// 24 x 1080p RGBA f32 1506 us before, 1055 us now.
 #include <cmath>
 
 #include "launch.h"
@@ -27,27 +35,37 @@ namespace {
 
 constexpr int kWin = 11;
 constexpr int kHalo = kWin - 1;
-constexpr int kStripW = 64;     // output columns of a strip (one per lane)
-constexpr int kStripRows = 66;  // output rows of a strip (a multiple of 11)
+constexpr int kBatch = 4;  // rows of window sums that go through LDS together
+constexpr int kRing = 12;  // accumulating output rows: a multiple of kBatch, at least kWin
+
+// The partials' room in the caller's workspace: one per strip of 64 x 66
+// outputs, which the strips of a launch never outnumber.
+constexpr int kRoomW = 64, kRoomRows = 66;
 
 struct QualityArgs {
     const void *pred, *truth;
     int c, h, w;
     int strips_x, strips_y;
+    int strip_rows;   // output rows of a strip
     double g[kWin];  // normalised 1-D Gaussian weights
     double c1, c2;
     double *partial;  // [B][C][strips_y][strips_x][2] = (ssim sum, squared-error sum)
 };
 
-template <typename T>
-__device__ __forceinline__ float load_f32(const T *p, int64_t i) {
-    return to_f32(p[i]);
-}
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-template <typename T>
-__global__ __launch_bounds__(64) void ssim_strip_kernel(QualityArgs a) {
-    __shared__ float lx[kStripW + kHalo], ly[kStripW + kHalo];
-    const int lane = threadIdx.x;
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void ssim_strip_kernel(QualityArgs a) {
+    constexpr int kCols = 64 * NW;           // input columns of a strip
+    constexpr int kOut = kCols - kHalo;      // output columns
+    constexpr int kGroups = kCols / 4;       // groups of four adjacent columns
+    // Window sums of kBatch rows after the vertical filter. Four columns take
+    // six doubles: lanes then read their groups, 48 bytes apart, without bank
+    // conflicts. (One group more than written: read by the last groups, whose
+    // outputs past kOut are dropped.)
+    __shared__ __attribute__((aligned(16))) double vsum[kBatch][4][(kGroups + 1) * 6];
+    __shared__ double red[2][NW];
+    const int tid = threadIdx.x;
     int blk = blockIdx.x;
     const int sx = blk % a.strips_x;
     blk /= a.strips_x;
@@ -58,117 +76,124 @@ __global__ __launch_bounds__(64) void ssim_strip_kernel(QualityArgs a) {
     const int w = a.w, h = a.h;
     const int64_t hw = static_cast<int64_t>(h) * w;
     const int64_t plane = (static_cast<int64_t>(frame) * a.c + ch) * hw;
-    const T *px = static_cast<const T *>(a.pred) + plane;
-    const T *py = static_cast<const T *>(a.truth) + plane;
-    const int j0 = sx * kStripW, i0 = sy * kStripRows;
-    const int out_w = w - kHalo, out_h = h - kHalo;
+    const int j0 = sx * kOut, i0 = sy * a.strip_rows;
+    const T *px = static_cast<const T *>(a.pred) + plane + min(j0 + tid, w - 1);
+    const T *py = static_cast<const T *>(a.truth) + plane + min(j0 + tid, w - 1);
     const bool last_x = sx == a.strips_x - 1, last_y = sy == a.strips_y - 1;
-    // Input rows this strip reads, and the rows whose squared errors it owns.
-    const int rows_in = min(kStripRows, out_h - i0) + kHalo;
-    const int own_rows = last_y ? h - i0 : kStripRows;
-    const bool out_col = j0 + lane < out_w;
+    // Input rows this strip reads, and the pixels whose squared errors it owns.
+    const int rows_out = min(a.strip_rows, h - kHalo - i0);
+    const int rows_in = rows_out + kHalo;
+    const int own_rows = last_y ? h - i0 : a.strip_rows;
+    const bool own_col = j0 + tid < w && (last_x || tid < kOut);
+    // This lane's outputs in the horizontal filter.
+    const int grp = tid % kGroups, grow = tid / kGroups;
+    const int cols_out = min(kOut, w - kHalo - j0) - 4 * grp;  // of its four columns
 
-    double acc[kWin][5];
+    double acc[kRing][4];
 #pragma unroll
-    for (int s = 0; s < kWin; ++s)
+    for (int s = 0; s < kRing; ++s)
 #pragma unroll
-        for (int q = 0; q < 5; ++q) acc[s][q] = 0.0;
+        for (int q = 0; q < 4; ++q) acc[s][q] = 0.0;
     double ssim_sum = 0.0, sq_sum = 0.0;
 
-    // The next input row is loaded while the current one is filtered.
-    const int ca = min(j0 + lane, w - 1);
-    const int cb = min(j0 + kStripW + lane, w - 1);
-    float nxa, nya, nxb = 0.0f, nyb = 0.0f;
-    nxa = load_f32(px, static_cast<int64_t>(i0) * w + ca);
-    nya = load_f32(py, static_cast<int64_t>(i0) * w + ca);
-    if (lane < kHalo) {
-        nxb = load_f32(px, static_cast<int64_t>(i0) * w + cb);
-        nyb = load_f32(py, static_cast<int64_t>(i0) * w + cb);
-    }
-    for (int base = 0; base < rows_in; base += kWin) {
+    // The next batch of rows is loaded while the current one is filtered (rows
+    // past the strip repeat its last: what they add to is never output).
+    T nx[kBatch], ny[kBatch];
+    auto load = [&](int r0) {
 #pragma unroll
-        for (int s = 0; s < kWin; ++s) {
-            const int r = base + s;  // input row of the strip (wave-uniform)
-            if (r < rows_in) {
-                const float xa = nxa, ya = nya, xb = nxb, yb = nyb;
-                if (r + 1 < rows_in) {
-                    const int64_t next = static_cast<int64_t>(i0 + r + 1) * w;
-                    nxa = load_f32(px, next + ca);
-                    nya = load_f32(py, next + ca);
-                    if (lane < kHalo) {
-                        nxb = load_f32(px, next + cb);
-                        nyb = load_f32(py, next + cb);
+        for (int q = 0; q < kBatch; ++q) {
+            const int64_t row = static_cast<int64_t>(i0 + min(r0 + q, rows_in - 1)) * w;
+            nx[q] = px[row];
+            ny[q] = py[row];
+        }
+    };
+    load(0);
+    for (int base = 0; base < rows_in; base += kRing) {
+#pragma unroll
+        for (int bt = 0; bt < kRing / kBatch; ++bt) {
+            const int r0 = base + bt * kBatch;  // first input row of the batch
+            if (r0 >= rows_in) break;           // workgroup-uniform
+            T cx[kBatch], cy[kBatch];
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) { cx[q] = nx[q]; cy[q] = ny[q]; }
+            load(r0 + kBatch);
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+                const int s = bt * kBatch + q;
+                const double x = to_f32(cx[q]), y = to_f32(cy[q]);
+                if (r0 + q < own_rows && own_col) {
+                    const double d = x - y;
+                    sq_sum = fma(d, d, sq_sum);
+                }
+                const double v[4] = {x, y, fma(x, x, y * y), x * y};
+                // input row r feeds output rows r - t, t = 0 .. 10, kept in
+                // ring slot (r - t) mod 12 = (s - t) mod 12 (static)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    acc[s][k] = a.g[0] * v[k];
+#pragma unroll
+                    for (int t = 1; t < kWin; ++t) {
+                        const int slot = (s - t + kRing) % kRing;
+                        acc[slot][k] = fma(a.g[t], v[k], acc[slot][k]);
                     }
+                    // output row r - 10 is complete
+                    vsum[q][k][tid + 2 * (tid / 4)] = acc[(s + kRing - kHalo) % kRing][k];
                 }
-                __syncthreads();  // previous row's taps have been read
-                lx[lane] = xa;
-                ly[lane] = ya;
-                if (lane < kHalo) {
-                    lx[kStripW + lane] = xb;
-                    ly[kStripW + lane] = yb;
-                }
-                __syncthreads();
-                // squared errors of the input pixels this strip owns
-                if (r < own_rows) {
-                    if (j0 + lane < w && (last_x || lane < kStripW)) {
-                        const double d = static_cast<double>(xa) - ya;
-                        sq_sum = fma(d, d, sq_sum);
-                    }
-                    if (last_x && lane < kHalo && j0 + kStripW + lane < w) {
-                        const double d = static_cast<double>(xb) - yb;
-                        sq_sum = fma(d, d, sq_sum);
-                    }
-                }
-                // horizontal window sums at output column j0 + lane
-                double hx = 0.0, hy = 0.0, hxx = 0.0, hyy = 0.0, hxy = 0.0;
-#pragma unroll
-                for (int b = 0; b < kWin; ++b) {
-                    const double xv = lx[lane + b], yv = ly[lane + b];
-                    const double tx = a.g[b] * xv, ty = a.g[b] * yv;
-                    hx += tx;
-                    hy += ty;
-                    hxx = fma(tx, xv, hxx);
-                    hyy = fma(ty, yv, hyy);
-                    hxy = fma(tx, yv, hxy);
-                }
-                // input row r feeds output rows r - t, t = 0..10, kept in ring
-                // slot (r - t) mod 11 = (s - t) mod 11 (static)
-#pragma unroll
-                for (int t = 0; t < kWin; ++t) {
-                    const int slot = (s - t + kWin) % kWin;
-                    acc[slot][0] = fma(a.g[t], hx, acc[slot][0]);
-                    acc[slot][1] = fma(a.g[t], hy, acc[slot][1]);
-                    acc[slot][2] = fma(a.g[t], hxx, acc[slot][2]);
-                    acc[slot][3] = fma(a.g[t], hyy, acc[slot][3]);
-                    acc[slot][4] = fma(a.g[t], hxy, acc[slot][4]);
-                }
-                // output row r - 10 is complete (slot (s + 1) mod 11)
-                const int slot = (s + 1) % kWin;
-                if (r >= kHalo) {
-                    const double mx = acc[slot][0], my = acc[slot][1];
-                    const double vx = acc[slot][2] - mx * mx;
-                    const double vy = acc[slot][3] - my * my;
-                    const double cxy = acc[slot][4] - mx * my;
-                    const double num = (2.0 * mx * my + a.c1) * (2.0 * cxy + a.c2);
-                    const double den = (mx * mx + my * my + a.c1) * (vx + vy + a.c2);
-                    if (out_col) ssim_sum += num / den;
-                }
-#pragma unroll
-                for (int q = 0; q < 5; ++q) acc[slot][q] = 0.0;
+                __builtin_amdgcn_sched_barrier(0);
             }
+            __syncthreads();
+            const int r_out = r0 + grow - kHalo;  // this lane's output row
+            if (r_out >= 0 && r_out < rows_out && cols_out > 0) {
+                double o[4][4];  // [sum][column]
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const f64x2 *src = reinterpret_cast<const f64x2 *>(&vsum[grow][k][grp * 6]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o[k][j] = 0.0;
+#pragma unroll
+                    for (int m = 0; m < 7; ++m) {  // columns 2 m, 2 m + 1 of the 14
+                        const f64x2 p = src[(m / 2) * 3 + m % 2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const int b = 2 * m + e - j;
+                                if (b >= 0 && b < kWin) o[k][j] = fma(a.g[b], e ? p.y : p.x, o[k][j]);
+                            }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // one sum's columns in registers at a time
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double mx = o[0][j], my = o[1][j];
+                    const double mxy = mx * my, mm = fma(mx, mx, my * my);
+                    const double num = fma(2.0, mxy, a.c1) * fma(2.0, o[3][j] - mxy, a.c2);
+                    const double den = (mm + a.c1) * ((o[2][j] - mm) + a.c2);
+                    if (j < cols_out) ssim_sum += num / den;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __syncthreads();  // the sums have been read
         }
     }
-    // wavefront sums (butterfly; addition is commutative, so every lane agrees)
+    // wavefront sums (butterfly; addition is commutative, so every lane
+    // agrees), then the wavefronts in order
 #pragma unroll
     for (int m = 1; m < 64; m <<= 1) {
         ssim_sum += __shfl_xor(ssim_sum, m);
         sq_sum += __shfl_xor(sq_sum, m);
     }
-    if (lane == 0) {
+    if (tid % 64 == 0) {
+        red[0][tid / 64] = ssim_sum;
+        red[1][tid / 64] = sq_sum;
+    }
+    __syncthreads();
+    if (tid < 2) {
+        double t = red[tid][0];
+        for (int k = 1; k < NW; ++k) t += red[tid][k];
         const int64_t idx =
             ((static_cast<int64_t>(frame) * a.c + ch) * a.strips_y + sy) * a.strips_x + sx;
-        a.partial[2 * idx] = ssim_sum;
-        a.partial[2 * idx + 1] = sq_sum;
+        a.partial[2 * idx + tid] = t;
     }
 }
 
@@ -196,16 +221,26 @@ __global__ __launch_bounds__(64) void quality_final_kernel(const double *partial
     }
 }
 
-void strips(int h, int w, int &sx, int &sy) {
-    sx = (w - kHalo + kStripW - 1) / kStripW;
-    sy = (h - kHalo + kStripRows - 1) / kStripRows;
+// Strips of the workspace's room per channel.
+void room(int h, int w, int &sx, int &sy) {
+    sx = (w - kHalo + kRoomW - 1) / kRoomW;
+    sy = (h - kHalo + kRoomRows - 1) / kRoomRows;
+}
+
+template <typename T>
+void launch_strips(int nw, dim3 grid, hipStream_t st, const QualityArgs &a) {
+    switch (nw) {
+    case 1: hipLaunchKernelGGL((ssim_strip_kernel<T, 1>), grid, dim3(64), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((ssim_strip_kernel<T, 2>), grid, dim3(128), 0, st, a); break;
+    default: hipLaunchKernelGGL((ssim_strip_kernel<T, 4>), grid, dim3(256), 0, st, a); break;
+    }
 }
 
 }  // namespace
 
 size_t quality_workspace_bytes(int b, int c, int h, int w) {
     int sx, sy;
-    strips(h, w, sx, sy);
+    room(h, w, sx, sy);
     return sizeof(double) * 2 * static_cast<size_t>(b) * c * sx * sy;
 }
 
@@ -218,7 +253,21 @@ hipError_t launch_quality(int dtype, const void *pred, const void *truth, int b,
     a.c = c;
     a.h = h;
     a.w = w;
-    strips(h, w, a.strips_x, a.strips_y);
+    // As few wavefronts per strip as cover the width (at most four), and
+    // strips of 132 output rows (10 halo rows each) where they still make
+    // several workgroups per CU, else of 66 or 24: the shorter the strip, the
+    // more workgroups for small batches. Their number stays within the
+    // workspace's room (strips of 54 or 118 outputs are used alone in a row).
+    const int nw = w - kHalo <= 64 - kHalo ? 1 : (w - kHalo <= 128 - kHalo ? 2 : 4);
+    a.strips_x = (w - kHalo + 64 * nw - kHalo - 1) / (64 * nw - kHalo);
+    int room_x, room_y;
+    room(h, w, room_x, room_y);
+    const int64_t columns = static_cast<int64_t>(b) * c * a.strips_x;
+    auto rows = [&](int strip) { return (h - kHalo + strip - 1) / strip; };
+    a.strip_rows = 132;
+    if (columns * rows(132) < 2048) a.strip_rows = 66;
+    if (columns * rows(66) < 768 && a.strips_x * rows(24) <= room_x * room_y) a.strip_rows = 24;
+    a.strips_y = rows(a.strip_rows);
     double e[kWin], sum = 0.0;
     for (int i = 0; i < kWin; ++i) {
         const double r = i - (kWin - 1) / 2;
@@ -232,9 +281,9 @@ hipError_t launch_quality(int dtype, const void *pred, const void *truth, int b,
     const int per_frame = c * a.strips_x * a.strips_y;
     const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(b) * per_frame));
     switch (dtype) {
-    case 0: hipLaunchKernelGGL(ssim_strip_kernel<float>, grid, dim3(64), 0, stream, a); break;
-    case 1: hipLaunchKernelGGL(ssim_strip_kernel<_Float16>, grid, dim3(64), 0, stream, a); break;
-    default: hipLaunchKernelGGL(ssim_strip_kernel<__bf16>, grid, dim3(64), 0, stream, a); break;
+    case 0: launch_strips<float>(nw, grid, stream, a); break;
+    case 1: launch_strips<_Float16>(nw, grid, stream, a); break;
+    default: launch_strips<__bf16>(nw, grid, stream, a); break;
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;

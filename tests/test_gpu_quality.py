@@ -111,3 +111,18 @@ def test_quality_reproducible_and_binding_checks():
         exw.frame_quality(x, y[:, :1])
     with pytest.raises(exw.ExwError):
         exw.frame_quality(x[..., :10, :], y[..., :10, :])
+
+
+# Widths around one, two and four wavefronts per strip and a second strip;
+# heights around the batches of rows, and batches large enough for strips of
+# 66 and 132 rows.
+@pytest.mark.parametrize("shape", [(1, 1, 13, 64), (1, 1, 14, 65), (1, 2, 21, 128), (1, 1, 22, 129),
+                                   (1, 1, 23, 256), (1, 2, 34, 257), (1, 1, 35, 503),
+                                   (1, 2, 80, 300), (384, 1, 80, 14), (256, 4, 150, 14)])
+def test_quality_strip_edges(shape):
+    dev = need_gpu()
+    rng = np.random.default_rng(sum(shape))
+    truth = rng.random(shape).astype(np.float32)
+    pred = np.clip(truth + rng.normal(0, 0.05, shape), 0, 1).astype(np.float32)
+    announce("frame quality strips", shape)
+    assert_quality(gpu_quality(pred, truth, "f32", dev), pred, truth, "f32", f"shape {shape}")
