@@ -20,19 +20,20 @@
 // different banks), and adds the copies up at the end. Each lane takes 16
 // consecutive bytes of each buffer at a time: one load where single values
 // took four or eight, and neighbouring pixels, which tend to share a bin, in
-// one lane's sequence rather than in neighbouring lanes. The last workgroup of
+// one lane, which adds a run of them at once. The last workgroup of
 // a plane (by a ticket) scans the count differences in 64-bit integers and sums
 // their magnitudes exactly; the result is that exact sum / (H*W) * width in
 // float64. Integer counts make every result independent of the order of the
 // atomics.
 //
-// Bound: the LDS additions (one per value; lanes of one copy in one bin take
-// turns) and the float64 binning (six operations per value), with HBM close
-// behind on unlike values. Before (256 threads, single-value loads, a floor and
-// two float64 clamps per value, the sums in a launch of their own), call time:
-// three channels of 4 x 1440p f32, 1024 bins 104 us on smooth and 96 on random
-// values, now 93 and 83; bf16, 256 bins 88 and 54, now 80 and 43; one 1080p
-// frame f32 28, now 26; 2 x 481 x 270 19.9, now 16.1.
+// Bound: the LDS additions and the float64 binning (six operations per value),
+// with HBM close behind (4.4 TB/s on f32). Before (256 threads, single-value
+// loads, a floor and two float64 clamps per value, one addition per value, the
+// sums in a launch of their own), call time: three channels of 4 x 1440p f32,
+// 1024 bins 104 us on smooth, 96 on random and 100 on equal values, now 82, 81
+// and 81 (93, 83 and 99 with one addition per value); bf16, 256 bins 88, 54 and
+// 84, now 46, 46 and 44 (80, 43 and 84); one 1080p frame f32 28, now 25; 2 x 481
+// x 270 19.9, now 16.3.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -138,9 +139,22 @@ __global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
     const T *pb = static_cast<const T *>(a.prev) + static_cast<int64_t>(plane) * a.hw;
     const int64_t begin = static_cast<int64_t>(part) * a.run;
     const int64_t end = min(a.hw, begin + a.run);
-    auto count = [&](T va, T vb) {
-        atomicAdd(&hist[bin_of(to_f32(va), a.lo, a.scale, a.bins)], 1u);
-        atomicAdd(&hist[a.bins + bin_of(to_f32(vb), a.lo, a.scale, a.bins)], 1u);
+    auto bin = [&](T v) { return bin_of(to_f32(v), a.lo, a.scale, a.bins); };
+    // V neighbouring values: one addition per run of values of one bin.
+    auto count = [&](const vec &v, uint32_t *to) {
+        int run_bin = bin(v[0]);
+        uint32_t run = 1u;
+#pragma unroll
+        for (int q = 1; q < V; ++q) {
+            const int b = bin(v[q]);
+            if (b != run_bin) {
+                atomicAdd(&to[run_bin], run);
+                run = 0u;
+                run_bin = b;
+            }
+            ++run;
+        }
+        atomicAdd(&to[run_bin], run);
     };
     const int64_t whole = begin + (end - begin) / V * V;  // full loads end here
     int64_t i = begin + static_cast<int64_t>(threadIdx.x) * V;
@@ -152,11 +166,14 @@ __global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
             const int64_t j = i + kStep < whole ? i + kStep : i;  // (the next load is in flight)
             na = *reinterpret_cast<const vec *>(pa + j);
             nb = *reinterpret_cast<const vec *>(pb + j);
-#pragma unroll
-            for (int q = 0; q < V; ++q) count(va[q], vb[q]);
+            count(va, hist);
+            count(vb, hist + a.bins);
         }
     }
-    if (const int64_t t = whole + threadIdx.x; t < end) count(pa[t], pb[t]);
+    if (const int64_t t = whole + threadIdx.x; t < end) {
+        atomicAdd(&hist[bin(pa[t])], 1u);
+        atomicAdd(&hist[a.bins + bin(pb[t])], 1u);
+    }
     __syncthreads();
     uint32_t *g = a.counts + static_cast<int64_t>(plane) * 2 * a.bins;
     for (int k = threadIdx.x; k < 2 * a.bins; k += kEmdThreads) {

@@ -100,3 +100,23 @@ def test_plane_at_the_size_limit():
     assert same.cpu().tolist() == [[0.0]]
     del cur, prev
     torch.cuda.empty_cache()
+
+
+# Planes around one load of 16 bytes and one step of a workgroup, of odd size
+# (so that planes start at any multiple of a value), one and several workgroups
+# per plane, with runs of equal values of every length.
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 3, 1, 3), (1, 3, 1, 9), (2, 2, 3, 5), (1, 3, 67, 61),
+                                   (1, 2, 129, 127), (1, 1, 257, 511), (10, 60, 7, 11)])
+def test_runs_and_tails(shape, dtype):
+    dev = need_gpu()
+    rng = np.random.default_rng(sum(shape))
+    count = int(np.prod(shape))
+    bufs = []
+    for _ in range(2):
+        v = np.repeat(rng.uniform(-1.2, 1.2, count), rng.integers(1, 20, count))[:count]
+        bufs.append(v.reshape(shape).astype(np.float32))
+    announce("buffer EMD runs", shape, dtype)
+    got = gpu_emd(bufs[0], bufs[1], -1.0, 1.0, 64, dtype, dev)
+    ref = buffer_emd.buffer_emd(stored(bufs[0], dtype), stored(bufs[1], dtype), -1.0, 1.0, 64)
+    assert np.array_equal(got, ref), np.abs(got - ref).max()

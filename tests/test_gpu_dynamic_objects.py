@@ -141,3 +141,17 @@ def test_frame_at_the_size_limit():
         assert got.cpu().tolist() == [(side // 64) ** 2], (conn, got)
     del st
     torch.cuda.empty_cache()
+
+
+# Frames around one and two 64 x 32 tiles and around the eight pixels a thread
+# loads, at densities from a few pixels to nearly full.
+@pytest.mark.parametrize("h", [31, 32, 33, 65])
+@pytest.mark.parametrize("w", [7, 8, 9, 63, 64, 65, 129])
+def test_tile_edges(h, w):
+    dev = need_gpu()
+    rng = np.random.default_rng(1000 * h + w)
+    density = np.array([0.02, 0.3, 0.59, 0.7, 0.97])[:, None, None]
+    st = (rng.random((5, h, w)) < density).astype(np.uint8) * rng.choice(
+        np.array([1, 2, 16, 128, 255], np.uint8), (5, h, w))
+    announce("dynamic objects tiles", h, w)
+    check(st, f"tiles {h} x {w}", dev)
