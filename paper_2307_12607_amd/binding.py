@@ -27,16 +27,17 @@ def exw_dtype(t: torch.dtype) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()  # (an int: the argument types convert it)
 
 
 def _dev(t: torch.Tensor, name: str, device: torch.device) -> None:
+    if t.is_cuda and t.device == device and t.is_contiguous():
+        return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if t.device != device:
         raise ValueError(f"{name} is on {t.device}, expected {device}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _expect(t: Optional[torch.Tensor], name: str, shape: Sequence[int], dtype: torch.dtype,
@@ -44,7 +45,7 @@ def _expect(t: Optional[torch.Tensor], name: str, shape: Sequence[int], dtype: t
     if t is None:
         return
     _dev(t, name, device)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     if t.dtype != dtype:
         raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype}")
@@ -58,10 +59,17 @@ def _phases(phases) -> tuple:
     return arr, len(ph)
 
 
-def _stream(device: torch.device, stream) -> ctypes.c_void_p:
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(stream.cuda_stream)
+# The current stream's handle without building a Stream object (3 of the ~19 us
+# that a small forward call takes on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device: torch.device, stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def exw_warp_forward_batched(src: torch.Tensor, mv: torch.Tensor, phases, out: torch.Tensor,
