@@ -213,26 +213,43 @@ __device__ __forceinline__ void motion_grad_phase(const T *const *iplane, int w,
     };
     // Twelve 16-bit channels: every channel's samples are loaded, under one
     // column test, before any is used (4 x 1440p bf16: 940 -> 864 us; with
-    // the column test repeated per channel the gain was lost). Elsewhere
-    // each channel's loads come with its use: the batched form was 3-15 %
-    // slower for four 16-bit channels and for twelve float32 ones.
+    // the column test repeated per channel the gain was lost), and they wait
+    // as loaded, two to a register: widened at the load they took 99 VGPRs
+    // instead of 73, a third workgroup per CU. Elsewhere each channel's loads
+    // come with its use: the batched form was 3-15 % slower for four 16-bit
+    // channels and for twelve float32 ones.
     constexpr bool batch = CT == 12 && sizeof(T) == 2;
+    uint32_t p0[CT], p1[CT];  // the batch: left tap in the low half
     if constexpr (batch) {
         if (w >= 2) {  // wave-uniform
 #pragma unroll
             for (int ch = 0; ch < CT; ++ch) {
-                load_pair(at(iplane[ch], o0), a0[ch], b0[ch]);
-                load_pair(at(iplane[ch], o1), a1[ch], b1[ch]);
+                p0[ch] = *reinterpret_cast<const u32_u *>(at(iplane[ch], o0));
+                p1[ch] = *reinterpret_cast<const u32_u *>(at(iplane[ch], o1));
             }
-        } else {
+        } else {  // both horizontal taps are column 0
+            auto both = [&](int ch, int row) -> uint32_t {
+                return 0x10001u * *reinterpret_cast<const uint16_t *>(
+                                      at(iplane[ch], static_cast<uint32_t>(row)));
+            };
 #pragma unroll
-            for (int ch = 0; ch < CT; ++ch) load_channel(ch);
+            for (int ch = 0; ch < CT; ++ch) {
+                p0[ch] = both(ch, t.ay.i0);
+                p1[ch] = both(ch, t.ay.i1);
+            }
         }
     }
     float su = 0.0f, sv = 0.0f;
 #pragma unroll
     for (int ch = 0; ch < CT; ++ch) {
-        if constexpr (!batch) load_channel(ch);
+        if constexpr (batch) {
+            a0[ch] = half_bits_to_f32(p0[ch], static_cast<T *>(nullptr));
+            b0[ch] = half_bits_to_f32(p0[ch] >> 16, static_cast<T *>(nullptr));
+            a1[ch] = half_bits_to_f32(p1[ch], static_cast<T *>(nullptr));
+            b1[ch] = half_bits_to_f32(p1[ch] >> 16, static_cast<T *>(nullptr));
+        } else {
+            load_channel(ch);
+        }
         const float i00 = last ? b0[ch] : a0[ch], i01 = b0[ch];
         const float i10 = last ? b1[ch] : a1[ch], i11 = b1[ch];
         const float dsx = fmaf(fy, i11 - i10, (1.0f - fy) * (i01 - i00));
@@ -257,16 +274,20 @@ __device__ __forceinline__ float shift_up1(float v) {
 // paid in wavefronts in flight. Four channels, three phases: 80 VGPRs allow 24
 // wavefronts per CU, so three workgroups of 8 must fit the 160 KB of LDS: 12
 // rows (8 x 1080p f32 472 us, f16 439; 16 rows, two workgroups: 506 and 511;
-// 8 rows in 4 wavefronts: 511 and 514). Twelve channels: 6 rows, two
-// workgroups (4 x 1440p bf16 538 us; 4, 5 and 8 rows: 619, 588 and 779); from
-// three phases on, their registers leave room for 4 wavefronts per workgroup
-// (2 x 1440p bf16: three phases, 4 rows 650 us, 6 rows 809, 6 rows in 8
-// wavefronts 888; four phases, 6 rows 1142, 4 rows 1253). One to three channels: three or four workgroups fit as they are (24 or 32 rows
-// for three channels: 353 against 324 us under i.i.d. motion).
-template <int CT, int KT>
+// 8 rows in 4 wavefronts: 511 and 514). Twelve channels, one phase: in 16 bits
+// 73 VGPRs, so three workgroups of 4 rows fit (4 x 1440p bf16 507 us; 5 rows
+// 575, 6 rows 545; i.i.d. motion pays for the smaller tile, 961 us against
+// 920); in float32 105, so two of 6 rows. Two phases: 6 rows (2 x 1440p bf16
+// 416 us, 4 rows 452). From three on, their registers leave room for 4
+// wavefronts per workgroup (2 x 1440p bf16: three phases, 4 rows 650 us, 6
+// rows 809, 6 rows in 8 wavefronts 888; four phases, 6 rows 1142, 4 rows
+// 1700). One to three channels: three or four workgroups fit as they are (24
+// or 32 rows for three channels: 353 against 324 us under i.i.d. motion).
+template <typename T, int CT, int KT>
 struct TileShape {
+    static constexpr int rows12 = KT == 3 || (KT == 1 && sizeof(T) == 2) ? 4 : 6;
     static constexpr int W = 128;
-    static constexpr int H = CT == 1 ? 32 : (CT <= 3 ? 16 : (CT == 4 ? 12 : (KT == 3 ? 4 : 6)));
+    static constexpr int H = CT == 1 ? 32 : (CT <= 3 ? 16 : (CT == 4 ? 12 : rows12));
     static constexpr int waves = CT == 12 && KT >= 3 ? 4 : 8;
     static constexpr int cells = W * H;
     // Candidate segments: rows within kFar of the tile, at most 8 columns.
@@ -323,8 +344,8 @@ struct SegLoad {
 // into registers (a strip of 128 x 8 pixels per wavefront: 640 us, since the
 // motion and samples re-read per phase miss the L2).
 template <typename T, int CT, int KT>
-__global__ __launch_bounds__((TileShape<CT, KT>::waves * kSegW)) void adjoint_tiles_kernel(BwdArgs<T> a) {
-    using Tile = TileShape<CT, KT>;
+__global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint_tiles_kernel(BwdArgs<T> a) {
+    using Tile = TileShape<T, CT, KT>;
     constexpr int TW = Tile::W, TH = Tile::H, NW = Tile::waves;
     __shared__ __attribute__((aligned(16))) double acc[CT * Tile::cells];  // [CT][TH][TW]
     __shared__ uint16_t list[Tile::max_cand];
@@ -945,7 +966,7 @@ hipError_t run(BwdArgs<T> a, const BwdWorkspace &ws, hipStream_t st) {
         (e = footprint_pass<KT>(a.mv, a.boxes, a.offs, a.info, a.n, a.h, a.w, a.s, st)) != hipSuccess)
         return e;
 
-    using Tile = TileShape<CT, KT>;
+    using Tile = TileShape<T, CT, KT>;
     a.tiles_x = (a.w + Tile::W - 1) / Tile::W;
     a.tiles_y = (a.h + Tile::H - 1) / Tile::H;
     const int64_t tiles = static_cast<int64_t>(a.n) * a.tiles_x * a.tiles_y;

@@ -13,8 +13,8 @@ from gpu_util import announce, half_ulp, need_gpu, stored, to_dev, to_host
 pytestmark = pytest.mark.gpu
 
 # (channels, phases, tile rows): one entry per tile shape of the kernel
-SHAPES = [(1, 1, 32), (2, 3, 16), (3, 1, 16), (3, 3, 16), (4, 3, 12), (4, 4, 12), (12, 1, 6),
-          (12, 3, 4), (12, 4, 6)]
+SHAPES = [(1, 1, 32), (2, 3, 16), (3, 1, 16), (3, 3, 16), (4, 3, 12), (4, 4, 12), (12, 1, 4),
+          (12, 1, 6), (12, 2, 6), (12, 3, 4), (12, 4, 6)]
 PHASES = [0.25, 0.5, 0.75, 1.0]
 
 
@@ -36,7 +36,8 @@ def test_tile_edges(c, k, rows, dtype):
     dev = need_gpu()
     phases = [1.0] if k == 1 else PHASES[:k]
     rng = np.random.default_rng(100 * c + k)
-    for h, w in ((rows - 1, 127), (rows, 128), (rows + 1, 129), (2 * rows + 1, 191), (3, 2)):
+    for h, w in ((rows - 1, 127), (rows, 128), (rows + 1, 129), (2 * rows + 1, 191), (3, 2),
+                 (5, 1)):
         announce("tiles", c, k, h, w, dtype)
         src = rng.random((1, c, h, w), dtype=np.float32)
         mv = mixed_motion(rng, h, w)
