@@ -71,14 +71,15 @@ def algorithmic_bytes(n, c, h, w, k, b):
 
 def ssim_flops_per_position() -> float:
     """Float64 operations of the SSIM filter per output position and channel
-    (an FMA counts 2), from the strip kernel's separable scheme: each input
-    row is filtered horizontally (11 taps x (2 mul + 2 add + 3 FMA) = 110)
-    and added into the 11 output rows it feeds (11 x 5 FMA = 110); a strip of
-    66 output rows reads 76 input rows, so both are paid 76/66 times per
-    output row; the index itself is ~20 operations (3 products, 3
-    differences, the numerator's and denominator's sums and products, the
-    quotient, the running sum) and the squared error 3 (difference + FMA)."""
-    return (110.0 + 110.0) * 76.0 / 66.0 + 20.0 + 3.0
+    (an FMA counts 2), from the strip kernel's separable scheme at this size:
+    each input pixel forms x^2 + y^2 and x y (mul + FMA + mul = 4) and is added
+    into the 11 output rows it feeds (11 x 4 FMA = 88); a strip reads 256
+    columns and 142 rows for 246 x 132 outputs; each output then filters its
+    four sums horizontally (11 x 4 FMA = 88); the index itself is ~20
+    operations (3 products, 3 differences, the numerator's and denominator's
+    sums and products, the quotient, the running sum) and the squared error 3
+    (difference + FMA)."""
+    return (4.0 + 88.0) * (142.0 / 132.0) * (256.0 / 246.0) + 88.0 + 20.0 + 3.0
 
 
 def _elf_section(path, name):
