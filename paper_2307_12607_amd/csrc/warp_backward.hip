@@ -314,7 +314,7 @@ struct SegLoad {
 // wavefront only. (Before: one wavefront per 128 x 3 tile with float32 cells,
 // 2.8 replays per segment and turns for lanes that share a cell; 8 x 1080p
 // RGBA three phases f32 611 -> 472 us, f16 498 -> 439, 4 x 4K f16 841 -> 760,
-// 4 x 1440p 12-channel bf16 675 -> 538; under i.i.d. motion 8 x 1080p RGB one
+// 4 x 1440p 12-channel bf16 675 -> 507; under i.i.d. motion 8 x 1080p RGB one
 // phase 634 -> 324, RGBA three phases 3470 -> 690; a zooming camera, RGBA three
 // phases 712 -> 456.) The sums of a cell land in any order; rounded from
 // float64, they differ from run to run only where two orders straddle a
@@ -334,9 +334,9 @@ struct SegLoad {
 // samples of their motion gradient are aligned loads shared by the phases
 // whose offsets agree. Other segments add each lane's four taps.
 //
-// What bounds it: the vector ALU issues 55-60 % of the cycles and the LDS
-// additions 65 %, and neither covers the other at six wavefronts per SIMD;
-// HBM traffic is 1.2x the algorithmic bytes (2.1x before). Measured and left
+// What bounds it: the vector ALU issues 62 % of the cycles (f16: 75 %) and the
+// LDS additions 65 %, and neither covers the other at five to six wavefronts per SIMD;
+// HBM traffic is 1.23x the algorithmic bytes (2.1x before). Measured and left
 // out: lane 63's taps gathered into one addition (DPP moves cost more than
 // the additions they save: +6 %), every tap added by its own lane (+6 %), the
 // lower tap row carried in registers to the next segment (no gain), samples of
