@@ -395,36 +395,44 @@ __device__ __forceinline__ void store_pair(T *p, float a, float b) {
     *reinterpret_cast<u32_st *>(p) = static_cast<uint32_t>(ba) | (static_cast<uint32_t>(bb) << 16);
 }
 
-// Two pixels per lane: lane j owns pixels 2j and 2j+1 of the wavefront's
-// 128-pixel row segment. When every pixel is in the frame and each phase has
-// one integer tap offset for the whole segment, the pair's taps in a row are
-// columns c, c+1, c+2 (c = 2j minus the offset): one two-element load gives
-// c and c+1, lane j+1's first element is c+2 (a DPP shift; lane 63's come
-// from one load spread over lanes 0 .. 2C-1), and both outputs of a plane are
-// stored at once - half the memory instructions per pixel of the one-pixel
-// path. Phases with the offsets of the previous phase reuse its samples. The
+// Two pixels per lane of the wavefront's 128-pixel row segment, taken when
+// every pixel is in the frame and each phase has one integer tap offset for
+// the whole segment. Lane j owns pixels j and j + 64: their left taps are
+// two aligned single-element loads of 64 consecutive columns each, and their
+// right taps are lane j+1's left taps (a DPP shift; lane 63's are lane 0's
+// second one, and one load spread over lanes 0 .. 2C-1). ADJ (the kernels that
+// also form the statistics): lane j owns pixels 2j and 2j + 1, whose taps are
+// columns c, c+1 (one two-element load) and c+2 (lane j+1's first element), and
+// both outputs of a plane are stored at once. ADJ issues half the loads and
+// stores, but an 8-byte or misaligned load takes 16.7 cycles of a CU's texture
+// unit per wavefront where an aligned single one takes 5.2: split, 4 x 4K
+// RGBA f32 three phases 695 -> 665 us, 8 x 1080p 360 -> 346 (one phase 152 ->
+// 149), f16 246 -> 244. With the statistics, twelve 16-bit channels took 94
+// VGPRs instead of 63 that way.
+// Phases with the offsets of the previous phase reuse its samples. The
 // blend is that of the one-pixel path, term for term. (u0, v0), (u1, v1): the
 // motion of the lane's two pixels; after_first_loads() runs once the first
 // phase's gathers are issued. Returns false, having written nothing, when
 // the segment is not uniform; else true, with the offsets (ceil(s_k u),
 // ceil(s_k v)) of every phase in (orx, ory).
-template <typename T, int CT, int KT, typename Hook>
+template <bool ADJ, typename T, int CT, int KT, typename Hook>
 __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &g, float u0,
                                              float u1, float v0, float v1, int (&orx)[KT],
                                              int (&ory)[KT], Hook &&after_first_loads) {
     const int w = a.w, h = a.h, y = g.y;
     const int64_t hw = static_cast<int64_t>(h) * w;
     const uint32_t hw32 = static_cast<uint32_t>(hw);  // the frame spans less than 4 GB
-    const int x = g.sx0 + 2 * static_cast<int>(threadIdx.x);
+    constexpr int dx = ADJ ? 1 : kSegW;  // from the lane's first pixel to its second
+    const int x = g.sx0 + static_cast<int>(ADJ ? 2 * threadIdx.x : threadIdx.x);
     const uint32_t p = static_cast<uint32_t>(y) * static_cast<uint32_t>(w) + static_cast<uint32_t>(x);
     float fx0[KT], fx1[KT], fy0[KT], fy1[KT];
     int rx[KT], ry[KT];
     bool uni = true;
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
-        const Axis ax0 = split_axis(a.s[j] * u0, x, w), ax1 = split_axis(a.s[j] * u1, x + 1, w);
+        const Axis ax0 = split_axis(a.s[j] * u0, x, w), ax1 = split_axis(a.s[j] * u1, x + dx, w);
         const Axis ay0 = split_axis(a.s[j] * v0, y, h), ay1 = split_axis(a.s[j] * v1, y, h);
-        const int ox0 = x - ax0.i0, ox1 = x + 1 - ax1.i0;
+        const int ox0 = x - ax0.i0, ox1 = x + dx - ax1.i0;
         const int oy0 = y - ay0.i0, oy1 = y - ay1.i0;
         rx[j] = __builtin_amdgcn_readfirstlane(ox0);
         ry[j] = __builtin_amdgcn_readfirstlane(oy0);
@@ -435,8 +443,8 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
     }
     if (__ballot(uni) != ~0ull) return false;
     const T *fin = a.src + static_cast<int64_t>(g.in) * CT * hw;
-    float s0[CT], t0[CT], s1[CT], t1[CT];  // columns c, c+1 of rows r0 and r1
-    float ex = 0.0f;                       // lane 63's column c+2, lanes 0 .. 2C-1
+    float s0[CT], t0[CT], s1[CT], t1[CT];  // columns c, c + dx of rows r0 and r1
+    float ex = 0.0f;  // the segment's last right tap, lanes 0 .. 2C-1
 #pragma unroll
     for (int j = 0; j < KT; ++j) {
         if (j == 0 || rx[j] != rx[j - 1] || ry[j] != ry[j - 1]) {  // wave-uniform
@@ -452,13 +460,20 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
             const T exr = *at(fin, cq * hw32 + (threadIdx.x < CT ? r0 : r1) + ce);
 #pragma unroll
             for (int ch = 0; ch < CT; ++ch) {
-                load_pair(at(fin, ch * hw32 + r0 + c), s0[ch], t0[ch]);
-                load_pair(at(fin, ch * hw32 + r1 + c), s1[ch], t1[ch]);
+                if constexpr (ADJ) {
+                    load_pair(at(fin, ch * hw32 + r0 + c), s0[ch], t0[ch]);
+                    load_pair(at(fin, ch * hw32 + r1 + c), s1[ch], t1[ch]);
+                } else {
+                    s0[ch] = to_f32(*at(fin, ch * hw32 + r0 + c));
+                    t0[ch] = to_f32(*at(fin, ch * hw32 + r0 + c + dx));
+                    s1[ch] = to_f32(*at(fin, ch * hw32 + r1 + c));
+                    t1[ch] = to_f32(*at(fin, ch * hw32 + r1 + c + dx));
+                }
             }
             ex = to_f32(exr);
         }
         if (j == 0) after_first_loads();  // work that overlaps the gathers in flight
-        // pixel 2j: taps (s, t); pixel 2j+1: taps (t, next lane's s)
+        // a: the lane's first pixel, taps (s, m); b: its second, taps (t, n)
         const float a00 = (1.0f - fx0[j]) * (1.0f - fy0[j]), a01 = fx0[j] * (1.0f - fy0[j]);
         const float a10 = (1.0f - fx0[j]) * fy0[j], a11 = fx0[j] * fy0[j];
         const float b00 = (1.0f - fx1[j]) * (1.0f - fy1[j]), b01 = fx1[j] * (1.0f - fy1[j]);
@@ -468,19 +483,40 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
         for (int ch = 0; ch < CT; ++ch) {
             const int e0 = __builtin_amdgcn_readlane(__float_as_int(ex), ch);
             const int e1 = __builtin_amdgcn_readlane(__float_as_int(ex), CT + ch);
-            const float n0 = shift_down1_or(e0, s0[ch]), n1 = shift_down1_or(e1, s1[ch]);
+            float m0, m1, n0, n1;
+            if constexpr (ADJ) {
+                m0 = t0[ch]; m1 = t1[ch];
+                n0 = shift_down1_or(e0, s0[ch]); n1 = shift_down1_or(e1, s1[ch]);
+            } else {
+                const int f0 = __builtin_amdgcn_readfirstlane(__float_as_int(t0[ch]));
+                const int f1 = __builtin_amdgcn_readfirstlane(__float_as_int(t1[ch]));
+                m0 = shift_down1_or(f0, s0[ch]); m1 = shift_down1_or(f1, s1[ch]);
+                n0 = shift_down1_or(e0, t0[ch]); n1 = shift_down1_or(e1, t1[ch]);
+            }
             float acc0 = a00 * s0[ch];
-            acc0 = fmaf(a01, t0[ch], acc0);
+            acc0 = fmaf(a01, m0, acc0);
             acc0 = fmaf(a10, s1[ch], acc0);
-            acc0 = fmaf(a11, t1[ch], acc0);
+            acc0 = fmaf(a11, m1, acc0);
             float acc1 = b00 * t0[ch];
             acc1 = fmaf(b01, n0, acc1);
             acc1 = fmaf(b10, t1[ch], acc1);
             acc1 = fmaf(b11, n1, acc1);
-            store_pair(at(fout, p + ch * hw32), acc0, acc1);
+            if constexpr (ADJ) {
+                store_pair(at(fout, p + ch * hw32), acc0, acc1);
+            } else {
+                *at(fout, p + ch * hw32) = from_f32<T>(acc0);
+                *at(fout, p + ch * hw32 + dx) = from_f32<T>(acc1);
+            }
         }
-        if (a.mask)  // every pixel valid
-            *reinterpret_cast<u16_st *>(a.mask + (static_cast<int64_t>(g.in) * KT + j) * hw + p) = 0x0101;
+        if (a.mask) {  // every pixel valid
+            uint8_t *m = a.mask + (static_cast<int64_t>(g.in) * KT + j) * hw + p;
+            if constexpr (ADJ) {
+                *reinterpret_cast<u16_st *>(m) = 0x0101;
+            } else {
+                m[0] = 1;
+                m[dx] = 1;
+            }
+        }
     }
 #pragma unroll
     for (int j = 0; j < KT; ++j) { orx[j] = rx[j]; ory[j] = ry[j]; }
@@ -495,11 +531,10 @@ __device__ __forceinline__ bool pair_uniform_load(const FwdArgs<T> &a, const Seg
     const int64_t hw = static_cast<int64_t>(a.h) * a.w;
     const float *mu = a.mv + 2 * static_cast<int64_t>(g.in) * hw;
     const uint32_t p = static_cast<uint32_t>(g.y) * static_cast<uint32_t>(a.w) +
-                       static_cast<uint32_t>(g.sx0 + 2 * static_cast<int>(threadIdx.x));
-    float u0, u1, v0, v1;
-    load_pair(at(mu, p), u0, u1);
-    load_pair(at(mu + hw, p), v0, v1);
-    return pair_uniform<T, CT, KT>(a, g, u0, u1, v0, v1, orx, ory, [] {});
+                       static_cast<uint32_t>(g.sx0 + static_cast<int>(threadIdx.x));
+    const float u0 = *at(mu, p), u1 = *at(mu, p + kSegW);
+    const float v0 = *at(mu + hw, p), v1 = *at(mu + hw, p + kSegW);
+    return pair_uniform<false, T, CT, KT>(a, g, u0, u1, v0, v1, orx, ory, [] {});
 }
 
 // Footprint records of the wavefront's two 64-pixel segments after the
@@ -689,7 +724,7 @@ __global__ __launch_bounds__(kThreads) void warp_forward_kernel(FwdArgs<T> a) {
             int rx[KT], ry[KT];
             // (the sums are formed while the first gathers are in flight)
             if (a.frame_32bit && g.y < a.h && g.sx0 + kSegPair <= a.w &&
-                pair_uniform<T, CT, KT>(a, g, u0, u1, v0, v1, rx, ry, sums)) {
+                pair_uniform<true, T, CT, KT>(a, g, u0, u1, v0, v1, rx, ry, sums)) {
                 record_pair<T, KT>(a, g, rx, ry);
                 done = true;
             }

@@ -125,3 +125,18 @@ def test_rigid_forward_16bit_channel_counts(c, phases, dtype):
         assert np.array_equal(mask.cpu().numpy(), ref_mask)
         assert np.array_equal(cnt.cpu().numpy().astype(np.int64), ref_cnt)
         assert_close_kernel(to_host(out), ref, dtype, f"rigid c={c} {dtype} {w}")
+
+
+@pytest.mark.parametrize("w", [127, 128, 129, 256, 320])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_segment_halves_match_the_oracle(dtype, w):
+    """Frames a column short of, equal to and past the 128-pixel segments whose
+    two halves one wavefront warps together: the columns at the halves' seam
+    and at the segment's end take their right taps from elsewhere."""
+    dev = need_gpu()
+    c = 3 if w == 129 else 4
+    src = np.random.default_rng(w).random((1, c, 9, w)).astype(np.float32)
+    rect = (3, 5, max(0, w - 40), w - 8, 1.5, 0.5)
+    for px, py, phases in PANS[:5]:
+        for r in (None, rect):
+            run_case(src, pan_field(1, 9, w, px, py, r), phases, dtype, dev, f"halves {w} {px},{py}")
