@@ -531,7 +531,8 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
         // Motion gradient of the home segments (every pixel written once).
         if (a.gmv && (unsigned)(y - ty0) < (unsigned)TH && sx0 / TW == tx) {
             float gu = 0.0f, gv = 0.0f;
-            if (seg_uniform && a.frame_32bit) {
+            bool per_channel = !(seg_uniform && a.frame_32bit);
+            if (!per_channel) {
                 // The taps of a uniform segment are contiguous across lanes,
                 // so its samples are aligned, coalesced single-element loads.
                 // When all phases share their offsets (rigid motion slower
@@ -562,7 +563,8 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
                 // differences (upper and lower row along x, left and right
                 // column along y); the fractions are applied to the sums, as
                 // soon as a phase's are complete (kept for all phases they
-                // cost 12 registers: 8 x 1080p f32 472 -> 499 us).
+                // cost 12 registers: 8 x 1080p f32 472 -> 499 us). Pixels whose
+                // sums are not finite are formed again below.
                 float su[KT], sv[KT], s0[KT], s1[KT], s2[KT], s3[KT];
 #pragma unroll
                 for (int k = 0; k < KT; ++k)
@@ -627,7 +629,14 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
                     gu = fmaf(-a.s[k], su[k], gu);
                     gv = fmaf(-a.s[k], sv[k], gv);
                 }
-            } else {
+                // An infinite upstream gradient (overflowed loss scaling) makes
+                // the sums infinite, and a fraction of 0 times them a NaN,
+                // where the per-channel form, which applies the fractions to
+                // the finite samples, keeps the infinity.
+                per_channel = !(fabsf(gu) + fabsf(gv) < HUGE_VALF);
+                if (per_channel) gu = gv = 0.0f;
+            }
+            if (per_channel) {
 #pragma unroll
                 for (int k = 0; k < KT; ++k)
                     if (t[k].valid) motion_grad_phase<T, CT>(iplane, w, t[k], g[k], a.s[k], gu, gv);

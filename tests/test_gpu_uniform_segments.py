@@ -140,3 +140,35 @@ def test_segment_halves_match_the_oracle(dtype, w):
     for px, py, phases in PANS[:5]:
         for r in (None, rect):
             run_case(src, pan_field(1, 9, w, px, py, r), phases, dtype, dev, f"halves {w} {px},{py}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("c,pan,phases", [(1, (3.0, -2.0), (1.0,)), (4, (4.0, 8.0), (0.25, 0.5, 0.75)),
+                                          (3, (2.5, -1.25), (1.0,)), (12, (-2.0, 0.0), (1.0,)),
+                                          (4, (0.6, -0.8), (0.25, 0.5, 0.75))])
+def test_infinite_upstream_gradients(c, pan, phases, dtype):
+    """Upstream gradients with infinities (loss scaling that overflowed) in
+    rigid segments: the motion gradient is infinite, NaN and finite exactly
+    where the per-channel sum g * d out / d(sx, sy) is, also at integer
+    displacements, whose fractions are 0."""
+    dev = need_gpu()
+    rng = np.random.default_rng(c)
+    src = rng.random((1, c, 20, 256)).astype(np.float32)
+    mv = pan_field(1, 20, 256, *pan)
+    g = rng.standard_normal((1, len(phases), c, 20, 256)).astype(np.float32)
+    for y, x, v in ((9, 70, np.inf), (10, 71, -np.inf), (11, 127, np.inf), (12, 128, -np.inf)):
+        g[0, 0, c // 2, y, x] = v
+    g[0, -1, 0, 9, 70] = np.inf  # a second phase or channel of one pixel
+    src_q, g_q = stored(src, dtype), stored(g, dtype)
+    announce("infinite upstream", c, pan, phases, dtype)
+    _, gm = exw.warp_backward(to_dev(src, dtype, dev), torch.from_numpy(mv).to(dev), phases,
+                              to_dev(g, dtype, dev))
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        _, ref = warp_oracle.backward(src_q, mv, list(phases), g_q)
+    got = to_host(gm)
+    assert np.isinf(ref).sum() >= 4
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    check_grad(got[fin], ref[fin], "finite pixels")
