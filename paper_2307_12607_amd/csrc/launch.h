@@ -14,6 +14,9 @@ namespace exw {
 // entry points outside api.cpp; returns st.
 exw_status report(exw_status st, const char *msg);
 
+// Work-items (workgroups times their size) of one launch: HIP refuses 2^32.
+constexpr int64_t kMaxWorkItems = (int64_t(1) << 32) - 1;
+
 struct WarpShape {
     int n, c, h, w, k;
     float phases[4];

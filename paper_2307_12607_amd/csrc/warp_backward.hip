@@ -960,6 +960,22 @@ hipError_t footprint_pass(const float *mv, Box *boxes, SegOffsets *offs, FrameIn
     return hipGetLastError();
 }
 
+// The arguments of the tile kernel from frame f on.
+template <typename T>
+BwdArgs<T> frames_from(BwdArgs<T> a, int64_t f) {
+    const int64_t hw = static_cast<int64_t>(a.h) * a.w, segs = static_cast<int64_t>(a.h) * a.segs;
+    if (a.src) a.src += f * a.c * hw;
+    a.mv += f * 2 * hw;
+    a.gout += f * a.k * a.c * hw;
+    if (a.gsrc) a.gsrc += f * a.c * hw;
+    if (a.gmv) a.gmv += f * 2 * hw;
+    if (a.accum32) a.accum32 += f * a.c * hw;
+    a.boxes += f * segs;
+    a.offs += f * segs;
+    a.info += f;
+    return a;
+}
+
 template <typename T, int CT, int KT>
 hipError_t run(BwdArgs<T> a, const BwdWorkspace &ws, hipStream_t st) {
     const int64_t segs_total = static_cast<int64_t>(a.n) * a.h * a.segs;
@@ -978,10 +994,18 @@ hipError_t run(BwdArgs<T> a, const BwdWorkspace &ws, hipStream_t st) {
     using Tile = TileShape<T, CT, KT>;
     a.tiles_x = (a.w + Tile::W - 1) / Tile::W;
     a.tiles_y = (a.h + Tile::H - 1) / Tile::H;
-    const int64_t tiles = static_cast<int64_t>(a.n) * a.tiles_x * a.tiles_y;
-    hipLaunchKernelGGL((adjoint_tiles_kernel<T, CT, KT>), dim3(static_cast<unsigned>(tiles)),
-                       dim3(Tile::waves * kSegW), 0, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // One launch, except for batches of millions of tiny frames, whose tiles
+    // would exceed a launch (a single frame never does: its sides are below
+    // 2^24 and its pixels at most 2^30, so at most 2^22 tiles).
+    const int64_t per_frame = static_cast<int64_t>(a.tiles_x) * a.tiles_y;
+    const int64_t group = kMaxWorkItems / (Tile::waves * kSegW) / per_frame;
+    for (int64_t f0 = 0; f0 < a.n; f0 += group) {
+        const int64_t frames = a.n - f0 < group ? a.n - f0 : group;
+        hipLaunchKernelGGL((adjoint_tiles_kernel<T, CT, KT>),
+                           dim3(static_cast<unsigned>(frames * per_frame)),
+                           dim3(Tile::waves * kSegW), 0, st, frames_from(a, f0));
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
 
     float *far_accum = ws.accum32 ? ws.accum32 : reinterpret_cast<float *>(a.gsrc);
     hipLaunchKernelGGL((adjoint_far_kernel<T, CT, KT>), dim3(kFarBlocks), dim3(kThreads), 0, st,

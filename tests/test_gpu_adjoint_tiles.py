@@ -58,3 +58,16 @@ def test_tile_edges(c, k, rows, dtype):
             bound = bound + half_ulp(ref_gs, dtype)
         assert (np.abs(to_host(gs) - ref_gs) <= bound).all(), (h, w)
         assert (np.abs(to_host(gm) - ref_gm) <= tol * np.maximum(1.0, abs_gm)).all(), (h, w)
+
+
+def test_more_frames_than_one_launch_of_tiles_holds():
+    """2^23 + 3 frames of one pixel: the tiles take two launches. Motion 0, so
+    the image gradient is the upstream gradient."""
+    dev = need_gpu()
+    n = (1 << 23) + 3
+    announce("tiny frames", n)
+    g = torch.arange(n, device=dev, dtype=torch.float32).view(n, 1, 1, 1, 1) - 0.5
+    gs, _ = exw.warp_backward(torch.ones(n, 1, 1, 1, device=dev), torch.zeros(n, 2, 1, 1, device=dev),
+                              [1.0], g)
+    torch.cuda.synchronize()
+    assert torch.equal(gs, g[:, 0])
