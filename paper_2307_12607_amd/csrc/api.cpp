@@ -505,8 +505,7 @@ exw_status exw_buffer_emd(const void *cur, const void *prev, exw_dtype dtype, in
     if (elems > kMaxElems)
         return fail(EXW_ERROR_UNSUPPORTED, "batch too large (%llu elements)",
                     (unsigned long long)elems);
-    // the planes index a 1-D grid: far below its limit (a plane has at most 128
-    // workgroups, the launch at most max(512, planes))
+    // (the launches split larger grids than HIP holds; this bounds their number)
     if (uint64_t(n) * uint64_t(c) * 128u >= (uint64_t(1) << 31))
         return fail(EXW_ERROR_UNSUPPORTED, "too many planes (%llu)",
                     (unsigned long long)(uint64_t(n) * uint64_t(c)));

@@ -224,8 +224,6 @@ hipError_t launch_buffer_emd(int dtype, const void *cur, const void *prev, int n
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     EmdArgs a;
-    a.cur = cur;
-    a.prev = prev;
     a.hw = static_cast<int64_t>(h) * w;
     // Workgroups per plane: about kEmdTarget over all planes (each adds its
     // histogram to the plane's counters at the end, so more cost more there),
@@ -236,22 +234,33 @@ hipError_t launch_buffer_emd(int dtype, const void *cur, const void *prev, int n
     a.run = ((a.hw + a.parts - 1) / a.parts + 7) / 8 * 8;
     a.parts = static_cast<int>((a.hw + a.run - 1) / a.run);
     a.width = (hi - lo) / static_cast<double>(bins);
-    a.emd = emd;
     a.lo = lo;
     a.scale = static_cast<double>(bins) / (hi - lo);
     a.bins = bins;
     a.stride = 2 * bins + 1;
     a.copies = 4;
     while (a.copies > 1 && a.copies * a.stride > kEmdLdsWords) a.copies /= 2;
-    a.counts = counts;
-    const dim3 grid(static_cast<unsigned>(planes * a.parts));
     const size_t lds = sizeof(uint32_t) * a.copies * a.stride;
-    switch (dtype) {
-    case 0: hipLaunchKernelGGL(emd_kernel<float>, grid, dim3(kEmdThreads), lds, stream, a); break;
-    case 1: hipLaunchKernelGGL(emd_kernel<_Float16>, grid, dim3(kEmdThreads), lds, stream, a); break;
-    default: hipLaunchKernelGGL(emd_kernel<__bf16>, grid, dim3(kEmdThreads), lds, stream, a); break;
+    const dim3 block(kEmdThreads);
+    // One launch, except for batches of millions of tiny planes (a plane has at
+    // most kEmdTarget workgroups, so any plane fits a launch).
+    const int64_t group = kMaxWorkItems / kEmdThreads / a.parts;
+    const int64_t plane_bytes = a.hw * (dtype == 0 ? 4 : 2);
+    for (int64_t p0 = 0; p0 < planes; p0 += group) {
+        const int64_t some = planes - p0 < group ? planes - p0 : group;
+        const dim3 grid(static_cast<unsigned>(some * a.parts));
+        a.cur = static_cast<const char *>(cur) + p0 * plane_bytes;
+        a.prev = static_cast<const char *>(prev) + p0 * plane_bytes;
+        a.counts = counts + p0 * 2 * bins;
+        a.emd = emd + p0;
+        switch (dtype) {
+        case 0: hipLaunchKernelGGL(emd_kernel<float>, grid, block, lds, stream, a); break;
+        case 1: hipLaunchKernelGGL(emd_kernel<_Float16>, grid, block, lds, stream, a); break;
+        default: hipLaunchKernelGGL(emd_kernel<__bf16>, grid, block, lds, stream, a); break;
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace exw

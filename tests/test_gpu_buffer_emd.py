@@ -120,3 +120,15 @@ def test_runs_and_tails(shape, dtype):
     got = gpu_emd(bufs[0], bufs[1], -1.0, 1.0, 64, dtype, dev)
     ref = buffer_emd.buffer_emd(stored(bufs[0], dtype), stored(bufs[1], dtype), -1.0, 1.0, 64)
     assert np.array_equal(got, ref), np.abs(got - ref).max()
+
+
+def test_more_planes_than_one_launch_holds():
+    """2^22 + 64 planes of one value: the distance is that of the two bins."""
+    dev = need_gpu()
+    n, c = (1 << 16) + 1, 64
+    announce("emd planes", n * c)
+    i = torch.arange(n * c, device=dev, dtype=torch.int64).view(n, c, 1, 1)
+    cur, prev = i % 4, i // 3 % 4
+    got = exw.buffer_emd(cur.float() + 0.5, prev.float() + 0.5, 0.0, 4.0, 4)
+    torch.cuda.synchronize()
+    assert torch.equal(got, (cur - prev).abs().to(torch.float64).view(n, c))

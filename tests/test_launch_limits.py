@@ -123,3 +123,26 @@ def test_adjoint_of_many_tiny_frames(launches_of, n, recorded):
     assert status == 0
     tiles = [r for r in launches if r[2] == 512]  # the tile kernel's workgroups
     assert_consecutive(covered(tiles, SRC[1], 4, 1), n)
+
+
+@pytest.mark.parametrize("c,hw", [(64, 1), (64, 128 * 128), (1, 30000 * 30000), (3, 1080 * 1920)])
+@pytest.mark.parametrize("n", [1, 1 << 16, (1 << 18) - 1])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_emd_of_many_planes(launches_of, c, hw, n, dtype):
+    """Up to 2^24 - 64 planes, as long as the batch is within 2^40 values."""
+    if n * c * hw > 1 << 40 or n * c >= 1 << 24:
+        pytest.skip("not accepted")
+    esize = 2 if dtype else 4
+    status, launches = launches_of("exw_buffer_emd", [
+        ("p", 1 << 42), ("p", 1 << 43), ("i", dtype), ("i", n), ("i", c), ("i", 1), ("i", hw),
+        ("d", -1.0), ("d", 1.0), ("i", 64), ("p", 1 << 40), ("p", 1 << 41), ("z", 1 << 40), ("p", 0)])
+    assert status == 0
+    # the histogram kernel starts from cur, the clearing one from the workspace
+    hist = [r for r in launches if r[3] >= 1 << 42]
+    parts = hist[0][1] // covered_planes(hist, n * c, hw * esize)
+    assert_consecutive(covered(hist, 1 << 42, hw * esize, parts), n * c)
+
+
+def covered_planes(hist, planes, plane_bytes):
+    """Planes of the first histogram launch: up to where the second one starts."""
+    return planes if len(hist) == 1 else (hist[1][3] - hist[0][3]) // plane_bytes
