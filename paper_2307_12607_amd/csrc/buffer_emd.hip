@@ -10,21 +10,21 @@
 // of the two unit-mass histograms is the L1 distance of their cumulative
 // histograms times the bin width.
 //
-// Workgroups of 1024 threads own a contiguous run of one plane of both
-// buffers, count into LDS histograms (integer LDS atomics; both buffers'
-// counts side by side) and add their non-zero bins to the plane's global
-// counters with one integer atomic each. Smooth buffers put many lanes of a
+// Workgroups of 1024 threads (256 for many small planes) own a contiguous run
+// of one plane of both buffers, count into LDS histograms (integer LDS atomics;
+// both buffers' counts side by side) and add their non-zero bins to the plane's
+// global counters with one integer atomic each. Smooth buffers put many lanes of a
 // wavefront in one bin, and atomics on one address serialise: the workgroup
 // keeps up to four copies of its histograms, lane l counting into copy l mod
 // copies (the copies one word apart, so one bin of different copies falls in
 // different banks), and adds the copies up at the end. Each lane takes 16
 // consecutive bytes of each buffer at a time: one load where single values
 // took four or eight, and neighbouring pixels, which tend to share a bin, in
-// one lane, which adds a run of them at once. The last workgroup of
-// a plane (by a ticket) scans the count differences in 64-bit integers and sums
-// their magnitudes exactly; the result is that exact sum / (H*W) * width in
-// float64. Integer counts make every result independent of the order of the
-// atomics.
+// one lane, which adds a run of them at once. The last workgroup of a plane (by
+// a ticket; the only one takes its LDS histograms as they are) scans the count
+// differences in 64-bit integers and sums their magnitudes exactly; the result
+// is that exact sum / (H*W) * width in float64. Integer counts make every result
+// independent of the order of the atomics.
 //
 // Bound: the LDS additions and the float64 binning (six operations per value),
 // with HBM close behind (4.4 TB/s on f32). Before (256 threads, single-value
@@ -43,10 +43,9 @@
 namespace exw {
 namespace {
 
-constexpr int kEmdThreads = 1024;
-constexpr int kEmdWaves = kEmdThreads / 64;
-constexpr int kEmdTarget = 512;                        // workgroups of a launch, about: two per CU
+constexpr int kEmdSlots = 512;                         // workgroups of 1024 the chip holds: two per CU
 constexpr int64_t kEmdRun = 8192;                      // values of a plane per workgroup, at least
+constexpr int64_t kEmdMerge = 128 * 1024;              // see emd_plan
 
 constexpr int kEmdLdsWords = 8200;                     // LDS words for the copies, at most (~32 KB)
 
@@ -74,9 +73,6 @@ __device__ __forceinline__ int bin_of(float v, double lo, double scale, int bins
     return min(max(i, 0), bins - 1);
 }
 
-__device__ __forceinline__ long long count_of(const uint32_t *p) {  // after the other workgroups' adds
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 __device__ __forceinline__ long long wave_sum_i64(long long v) {
 #pragma unroll
@@ -85,16 +81,18 @@ __device__ __forceinline__ long long wave_sum_i64(long long v) {
 }
 
 // S = sum_i |CA_i - CB_i| over the cumulative counts of one plane, in 64-bit
-// integers (exact), then S / (H*W) * width; by the whole workgroup.
-__device__ __forceinline__ void emd_of_plane(const EmdArgs &a, int plane, long long *lds) {
-    const uint32_t *ca = a.counts + static_cast<int64_t>(plane) * 2 * a.bins;
-    const uint32_t *cb = ca + a.bins;
+// integers (exact), then S / (H*W) * width; by the whole workgroup. diff(i):
+// the difference of the two buffers' counts of bin i.
+template <int NT, typename Diff>
+__device__ __forceinline__ void emd_of_plane(const EmdArgs &a, int plane, long long *lds,
+                                             Diff &&diff) {
+    constexpr int kWaves = NT / 64;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    const int per = (a.bins + kEmdThreads - 1) / kEmdThreads;
+    const int per = (a.bins + NT - 1) / NT;
     const int b0 = min(a.bins, static_cast<int>(threadIdx.x) * per);
     const int b1 = min(a.bins, b0 + per);
     long long run = 0;
-    for (int i = b0; i < b1; ++i) run += count_of(ca + i) - count_of(cb + i);
+    for (int i = b0; i < b1; ++i) run += diff(i);
     // exclusive scan of the threads' totals: within the wavefront, then over
     // the wavefronts' totals
     long long inc = run;
@@ -109,30 +107,30 @@ __device__ __forceinline__ void emd_of_plane(const EmdArgs &a, int plane, long l
     for (int k = 0; k < wave; ++k) cum += lds[k];
     long long s = 0;
     for (int i = b0; i < b1; ++i) {
-        cum += count_of(ca + i) - count_of(cb + i);
+        cum += diff(i);
         s += cum < 0 ? -cum : cum;
     }
     s = wave_sum_i64(s);
-    if (lane == 0) lds[kEmdWaves + wave] = s;
+    if (lane == 0) lds[kWaves + wave] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         long long t = 0;
-        for (int k = 0; k < kEmdWaves; ++k) t += lds[kEmdWaves + k];
+        for (int k = 0; k < kWaves; ++k) t += lds[kWaves + k];
         a.emd[plane] = static_cast<double>(t) / static_cast<double>(a.hw) * a.width;
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void emd_kernel(EmdArgs a) {
     extern __shared__ uint32_t lds[];  // [copies][stride]: [2][bins] and a pad word each
-    __shared__ long long scan[2 * kEmdWaves];
+    __shared__ long long scan[2 * (NT / 64)];
     __shared__ int last;
     constexpr int V = 16 / sizeof(T);  // values per load
     // (element-aligned: planes of odd size put them at any multiple of it)
     typedef T vec __attribute__((ext_vector_type(V), aligned(sizeof(T))));
     const int plane = static_cast<int>(blockIdx.x) / a.parts;
     const int part = static_cast<int>(blockIdx.x) - plane * a.parts;
-    for (int i = threadIdx.x; i < a.copies * a.stride; i += kEmdThreads) lds[i] = 0u;
+    for (int i = threadIdx.x; i < a.copies * a.stride; i += NT) lds[i] = 0u;
     __syncthreads();
     uint32_t *hist = lds + (static_cast<int>(threadIdx.x) & (a.copies - 1)) * a.stride;
     const T *pa = static_cast<const T *>(a.cur) + static_cast<int64_t>(plane) * a.hw;
@@ -158,7 +156,7 @@ __global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
     };
     const int64_t whole = begin + (end - begin) / V * V;  // full loads end here
     int64_t i = begin + static_cast<int64_t>(threadIdx.x) * V;
-    constexpr int64_t kStep = static_cast<int64_t>(kEmdThreads) * V;
+    constexpr int64_t kStep = static_cast<int64_t>(NT) * V;
     if (i < whole) {
         vec na = *reinterpret_cast<const vec *>(pa + i), nb = *reinterpret_cast<const vec *>(pb + i);
         for (; i < whole; i += kStep) {
@@ -175,12 +173,20 @@ __global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
         atomicAdd(&hist[a.bins + bin(pb[t])], 1u);
     }
     __syncthreads();
-    uint32_t *g = a.counts + static_cast<int64_t>(plane) * 2 * a.bins;
-    for (int k = threadIdx.x; k < 2 * a.bins; k += kEmdThreads) {
+    auto total = [&](int k) {  // count k over the copies
         uint32_t t = lds[k];
         for (int c = 1; c < a.copies; ++c) t += lds[c * a.stride + k];
-        if (t != 0u) atomicAdd(&g[k], t);
+        return t;
+    };
+    if (a.parts == 1) {  // every count of the plane is here
+        emd_of_plane<NT>(a, plane, scan, [&](int i) {
+            return static_cast<long long>(total(i)) - total(a.bins + i);
+        });
+        return;
     }
+    uint32_t *g = a.counts + static_cast<int64_t>(plane) * 2 * a.bins;
+    for (int k = threadIdx.x; k < 2 * a.bins; k += NT)
+        if (const uint32_t t = total(k); t != 0u) atomicAdd(&g[k], t);
     // Every addition of this workgroup has been made (they are device-wide
     // atomics, read back as such) before the ticket says so. One thread's fence
     // per workgroup: one per thread wrote the L2 back 1024 times (145 against
@@ -194,7 +200,10 @@ __global__ __launch_bounds__(kEmdThreads) void emd_kernel(EmdArgs a) {
     }
     __syncthreads();
     if (!last) return;
-    emd_of_plane(a, plane, scan);
+    auto count_of = [&](int k) -> long long {  // after the other workgroups' adds
+        return __hip_atomic_load(g + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    emd_of_plane<NT>(a, plane, scan, [&](int i) { return count_of(i) - count_of(a.bins + i); });
 }
 
 // The counters and the tickets (the first word of every result).
@@ -204,6 +213,47 @@ __global__ __launch_bounds__(256) void emd_zero_kernel(uint32_t *counts, int64_t
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     for (int64_t i = t; i < n; i += stride) counts[i] = 0u;
     for (int64_t i = t; i < planes; i += stride) emd[i] = 0.0;
+}
+
+// Workgroups per plane and their size.
+struct EmdPlan {
+    int parts, threads;
+};
+
+// Workgroups of 1024 work in rounds of kEmdSlots; a round takes the time of its
+// runs plus, where a plane has several workgroups, what it takes to merge and
+// hand over their counts, about that of kEmdMerge bytes of each buffer (17 to 21
+// us for 256 and 1024 bins). The parts that give the least of it, at runs of
+// kEmdRun values at least: as many as one round holds while there are few
+// planes (24 planes of 1440p: 21), one from a few hundred small planes on (900
+// planes of 480 x 270 f32, 1024 bins: 166 us, two parts 257, four 338), and a few
+// parts where that fills the last round (258 planes of 1080p bf16, 256 bins:
+// one part 662 us, two 529, three 483, five 467, nine 484, twenty 598).
+// Workgroups of 256 where the planes are small and many: there the clearing,
+// the barriers and the scan of the bins count (6000 planes of 64 x 64 f32, 256
+// bins: 34 us, 62 with 1024; 20000 of 16 x 16, 64 bins: 40 and 163). Many bins
+// keep the larger ones (6000 of 32 x 32, 4096 bins: 72 us, 100 with 256).
+EmdPlan emd_plan(int64_t planes, int64_t hw, int esize, int bins) {
+    const int64_t want = (hw + kEmdRun - 1) / kEmdRun;
+    auto rounds_time = [&](int64_t parts) {
+        const int64_t rounds = (planes * parts + kEmdSlots - 1) / kEmdSlots;
+        return rounds * (hw * esize / parts + (parts > 1 ? kEmdMerge : 0));
+    };
+    int64_t parts = 1, best = rounds_time(1);
+    const int64_t first = planes < kEmdSlots ? kEmdSlots / planes : 1;  // one round full
+    for (int64_t p = first < want ? first : want; p <= want && p <= first + 8; ++p)
+        if (const int64_t t = rounds_time(p); t < best) { parts = p; best = t; }
+    const bool small = planes > kEmdSlots && hw <= 32768 && bins <= 512;
+    return EmdPlan{static_cast<int>(parts), parts == 1 && small ? 256 : 1024};
+}
+
+template <typename T>
+void launch_hist(int threads, dim3 grid, const EmdArgs &a, hipStream_t st) {
+    const size_t lds = sizeof(uint32_t) * a.copies * a.stride;
+    if (threads == 256)
+        hipLaunchKernelGGL((emd_kernel<T, 256>), grid, dim3(256), lds, st, a);
+    else
+        hipLaunchKernelGGL((emd_kernel<T, 1024>), grid, dim3(1024), lds, st, a);
 }
 
 }  // namespace
@@ -217,34 +267,30 @@ hipError_t launch_buffer_emd(int dtype, const void *cur, const void *prev, int n
                              hipStream_t stream) {
     const int64_t planes = static_cast<int64_t>(n) * c;
     uint32_t *counts = static_cast<uint32_t *>(workspace);
-    const int64_t words = planes * 2 * bins;
-    const int64_t zero_blocks = (words + 255) / 256 < 1024 ? (words + 255) / 256 : 1024;
-    hipLaunchKernelGGL(emd_zero_kernel, dim3(static_cast<unsigned>(zero_blocks)), dim3(256), 0,
-                       stream, counts, words, emd, planes);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     EmdArgs a;
     a.hw = static_cast<int64_t>(h) * w;
-    // Workgroups per plane: about kEmdTarget over all planes (each adds its
-    // histogram to the plane's counters at the end, so more cost more there),
-    // of at least kEmdRun values; runs of a multiple of 16 bytes.
-    const int64_t want = (a.hw + kEmdRun - 1) / kEmdRun;
-    const int64_t most = planes < kEmdTarget ? kEmdTarget / planes : 1;
-    a.parts = static_cast<int>(want < most ? want : most);
-    a.run = ((a.hw + a.parts - 1) / a.parts + 7) / 8 * 8;
+    a.stride = 2 * bins + 1;
+    a.copies = 4;
+    while (a.copies > 1 && a.copies * a.stride > kEmdLdsWords) a.copies /= 2;
+    const EmdPlan plan = emd_plan(planes, a.hw, dtype == 0 ? 4 : 2, bins);
+    a.parts = plan.parts;
+    a.run = ((a.hw + a.parts - 1) / a.parts + 7) / 8 * 8;  // a multiple of 16 bytes
     a.parts = static_cast<int>((a.hw + a.run - 1) / a.run);
     a.width = (hi - lo) / static_cast<double>(bins);
     a.lo = lo;
     a.scale = static_cast<double>(bins) / (hi - lo);
     a.bins = bins;
-    a.stride = 2 * bins + 1;
-    a.copies = 4;
-    while (a.copies > 1 && a.copies * a.stride > kEmdLdsWords) a.copies /= 2;
-    const size_t lds = sizeof(uint32_t) * a.copies * a.stride;
-    const dim3 block(kEmdThreads);
+    hipError_t e = hipSuccess;
+    if (a.parts > 1) {
+        const int64_t words = planes * 2 * bins;
+        const int64_t blocks = (words + 255) / 256 < 1024 ? (words + 255) / 256 : 1024;
+        hipLaunchKernelGGL(emd_zero_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
+                           stream, counts, words, emd, planes);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     // One launch, except for batches of millions of tiny planes (a plane has at
-    // most kEmdTarget workgroups, so any plane fits a launch).
-    const int64_t group = kMaxWorkItems / kEmdThreads / a.parts;
+    // most kEmdSlots + 8 workgroups, so any plane fits a launch).
+    const int64_t group = kMaxWorkItems / plan.threads / a.parts;
     const int64_t plane_bytes = a.hw * (dtype == 0 ? 4 : 2);
     for (int64_t p0 = 0; p0 < planes; p0 += group) {
         const int64_t some = planes - p0 < group ? planes - p0 : group;
@@ -254,9 +300,9 @@ hipError_t launch_buffer_emd(int dtype, const void *cur, const void *prev, int n
         a.counts = counts + p0 * 2 * bins;
         a.emd = emd + p0;
         switch (dtype) {
-        case 0: hipLaunchKernelGGL(emd_kernel<float>, grid, block, lds, stream, a); break;
-        case 1: hipLaunchKernelGGL(emd_kernel<_Float16>, grid, block, lds, stream, a); break;
-        default: hipLaunchKernelGGL(emd_kernel<__bf16>, grid, block, lds, stream, a); break;
+        case 0: launch_hist<float>(plan.threads, grid, a, stream); break;
+        case 1: launch_hist<_Float16>(plan.threads, grid, a, stream); break;
+        default: launch_hist<__bf16>(plan.threads, grid, a, stream); break;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

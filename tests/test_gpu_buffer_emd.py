@@ -132,3 +132,24 @@ def test_more_planes_than_one_launch_holds():
     got = exw.buffer_emd(cur.float() + 0.5, prev.float() + 0.5, 0.0, 4.0, 4)
     torch.cuda.synchronize()
     assert torch.equal(got, (cur - prev).abs().to(torch.float64).view(n, c))
+
+
+# Many planes: small ones (workgroups of 256), small ones with many bins, one
+# workgroup per plane, and planes that several workgroups share although they
+# outnumber half a round of workgroups.
+@pytest.mark.parametrize("n,c,h,w,bins,dtype", [
+    (172, 3, 13, 17, 64, "f16"), (600, 1, 9, 31, 1024, "f32"), (513, 1, 1, 1, 1, "f32"),
+    (300, 2, 181, 182, 512, "bf16"), (86, 3, 450, 441, 256, "f32"), (257, 1, 701, 703, 256, "f16")])
+def test_batches_of_many_planes(n, c, h, w, bins, dtype):
+    dev = need_gpu()
+    rng = np.random.default_rng(n + bins)
+    cur = rng.normal(0, 0.5, (2, 1, h, w)).astype(np.float32)
+    prev = rng.normal(0.1, 0.4, (2, 1, h, w)).astype(np.float32)
+    ref = buffer_emd.buffer_emd(stored(cur, dtype), stored(prev, dtype), -1.0, 1.0, bins)
+    announce("emd many planes", n, c, h, w, bins, dtype)
+    which = torch.arange(n * c) % 2  # plane i holds content i % 2
+    spread = lambda x: to_dev(x, dtype, dev)[which.to(dev)].view(n, c, h, w)
+    got = exw.buffer_emd(spread(cur), spread(prev), -1.0, 1.0, bins)
+    torch.cuda.synchronize()
+    want = np.asarray(ref).reshape(2)[which.numpy()].reshape(n, c)
+    assert np.array_equal(got.cpu().numpy(), want)
