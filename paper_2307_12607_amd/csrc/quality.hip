@@ -44,7 +44,7 @@ constexpr int kRoomW = 64, kRoomRows = 66;
 
 struct QualityArgs {
     const void *pred, *truth;
-    int c, h, w;
+    int h, w;
     int strips_x, strips_y;
     int strip_rows;   // output rows of a strip
     double g[kWin];  // normalised 1-D Gaussian weights
@@ -70,12 +70,9 @@ __global__ __launch_bounds__(64 * NW, 2) void ssim_strip_kernel(QualityArgs a) {
     const int sx = blk % a.strips_x;
     blk /= a.strips_x;
     const int sy = blk % a.strips_y;
-    blk /= a.strips_y;
-    const int ch = blk % a.c;
-    const int frame = blk / a.c;
+    const int pl = blk / a.strips_y;  // channel plane: frame * C + channel
     const int w = a.w, h = a.h;
-    const int64_t hw = static_cast<int64_t>(h) * w;
-    const int64_t plane = (static_cast<int64_t>(frame) * a.c + ch) * hw;
+    const int64_t plane = pl * (static_cast<int64_t>(h) * w);
     const int j0 = sx * kOut, i0 = sy * a.strip_rows;
     const T *px = static_cast<const T *>(a.pred) + plane + min(j0 + tid, w - 1);
     const T *py = static_cast<const T *>(a.truth) + plane + min(j0 + tid, w - 1);
@@ -191,8 +188,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ssim_strip_kernel(QualityArgs a) {
     if (tid < 2) {
         double t = red[tid][0];
         for (int k = 1; k < NW; ++k) t += red[tid][k];
-        const int64_t idx =
-            ((static_cast<int64_t>(frame) * a.c + ch) * a.strips_y + sy) * a.strips_x + sx;
+        const int64_t idx = (static_cast<int64_t>(pl) * a.strips_y + sy) * a.strips_x + sx;
         a.partial[2 * idx + tid] = t;
     }
 }
@@ -248,9 +244,6 @@ hipError_t launch_quality(int dtype, const void *pred, const void *truth, int b,
                           int w, double peak, double *quality, void *workspace,
                           hipStream_t stream) {
     QualityArgs a;
-    a.pred = pred;
-    a.truth = truth;
-    a.c = c;
     a.h = h;
     a.w = w;
     // As few wavefronts per strip as cover the width (at most four), and
@@ -277,20 +270,31 @@ hipError_t launch_quality(int dtype, const void *pred, const void *truth, int b,
     for (int i = 0; i < kWin; ++i) a.g[i] = e[i] / sum;
     a.c1 = (0.01 * peak) * (0.01 * peak);
     a.c2 = (0.03 * peak) * (0.03 * peak);
-    a.partial = static_cast<double *>(workspace);
-    const int per_frame = c * a.strips_x * a.strips_y;
-    const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(b) * per_frame));
-    switch (dtype) {
-    case 0: launch_strips<float>(nw, grid, stream, a); break;
-    case 1: launch_strips<_Float16>(nw, grid, stream, a); break;
-    default: launch_strips<__bf16>(nw, grid, stream, a); break;
+    double *partial = static_cast<double *>(workspace);
+    const int64_t planes = static_cast<int64_t>(b) * c;
+    const int64_t per_plane = static_cast<int64_t>(a.strips_x) * a.strips_y;
+    // One launch, except for batches whose strips would exceed it (tens of
+    // millions of tiny planes).
+    const int64_t fit = kMaxWorkItems / (64 * nw) / per_plane;
+    const int64_t group = fit < 1 ? 1 : fit;
+    const int64_t plane_bytes = static_cast<int64_t>(h) * w * (dtype == 0 ? 4 : 2);
+    for (int64_t p0 = 0; p0 < planes; p0 += group) {
+        const int64_t some = planes - p0 < group ? planes - p0 : group;
+        const dim3 grid(static_cast<unsigned>(some * per_plane));
+        a.pred = static_cast<const char *>(pred) + p0 * plane_bytes;
+        a.truth = static_cast<const char *>(truth) + p0 * plane_bytes;
+        a.partial = partial + 2 * p0 * per_plane;
+        switch (dtype) {
+        case 0: launch_strips<float>(nw, grid, stream, a); break;
+        case 1: launch_strips<_Float16>(nw, grid, stream, a); break;
+        default: launch_strips<__bf16>(nw, grid, stream, a); break;
+        }
+        if (const hipError_t err = hipGetLastError(); err != hipSuccess) return err;
     }
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
     const double n_px = static_cast<double>(c) * h * w;
     const double n_pos = static_cast<double>(c) * (h - kHalo) * (w - kHalo);
     hipLaunchKernelGGL(quality_final_kernel, dim3(static_cast<unsigned>(b)), dim3(64), 0, stream,
-                       a.partial, per_frame, n_px, n_pos, peak, quality);
+                       partial, static_cast<int>(c * per_plane), n_px, n_pos, peak, quality);
     return hipGetLastError();
 }
 

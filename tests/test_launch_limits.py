@@ -146,3 +146,19 @@ def test_emd_of_many_planes(launches_of, c, hw, n, dtype):
 def covered_planes(hist, planes, plane_bytes):
     """Planes of the first histogram launch: up to where the second one starts."""
     return planes if len(hist) == 1 else (hist[1][3] - hist[0][3]) // plane_bytes
+
+
+@pytest.mark.parametrize("b,c,h,w", [(1, 1, 11, 11), (1 << 25, 1, 11, 65), (5, 1 << 23, 11, 65),
+                                     (1 << 24, 2, 11, 64), ((1 << 24) + 1, 1, 11, 139),
+                                     (24, 4, 1080, 1920)])
+@pytest.mark.parametrize("dtype", [0, 2])
+def test_quality_of_many_planes(launches_of, b, c, h, w, dtype):
+    esize = 2 if dtype else 4
+    status, launches = launches_of("exw_frame_quality", [
+        ("p", 1 << 43), ("p", 1 << 42), ("i", dtype), ("i", b), ("i", c), ("i", h), ("i", w),
+        ("d", 1.0), ("p", 1 << 40), ("p", 1 << 41), ("z", 1 << 40), ("p", 0)])
+    assert status == 0
+    # the strip kernel starts from pred, the fold of the frames from the workspace
+    strips = [r for r in launches if r[3] >= 1 << 43]
+    per_plane = strips[0][1] // covered_planes(strips, b * c, h * w * esize)
+    assert_consecutive(covered(strips, 1 << 43, h * w * esize, per_plane), b * c)
