@@ -74,12 +74,12 @@ def ssim_flops_per_position() -> float:
     (an FMA counts 2), from the strip kernel's separable scheme at this size:
     each input pixel forms x^2 + y^2 and x y (mul + FMA + mul = 4) and is added
     into the 11 output rows it feeds (11 x 4 FMA = 88); a strip reads 256
-    columns and 142 rows for 246 x 132 outputs; each output then filters its
+    columns and 144 rows for 246 x 134 outputs; each output then filters its
     four sums horizontally (11 x 4 FMA = 88); the index itself is ~20
     operations (3 products, 3 differences, the numerator's and denominator's
     sums and products, the quotient, the running sum) and the squared error 3
     (difference + FMA)."""
-    return (4.0 + 88.0) * (142.0 / 132.0) * (256.0 / 246.0) + 88.0 + 20.0 + 3.0
+    return (4.0 + 88.0) * (144.0 / 134.0) * (256.0 / 246.0) + 88.0 + 20.0 + 3.0
 
 
 def _elf_section(path, name):

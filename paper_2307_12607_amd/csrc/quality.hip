@@ -24,7 +24,7 @@
 // four values and convert, ~30 for the index. Filtering horizontally first,
 // each lane its own column from LDS (22 reads, 22 conversions, 7 operations per
 // tap for five sums) took ~190 and 15 % more for the halo rows:
-// 24 x 1080p RGBA f32 1506 us before, 1055 us now.
+// 24 x 1080p RGBA f32 1500 us before, 1034 us now.
 #include <cmath>
 
 #include "launch.h"
@@ -223,6 +223,64 @@ void room(int h, int w, int &sx, int &sy) {
     sy = (h - kHalo + kRoomRows - 1) / kRoomRows;
 }
 
+// Wavefronts per strip, strips across a plane and output rows of a strip.
+struct StripPlan {
+    int nw, strips_x, rows;
+};
+
+// The plan of least estimated time, in units of one operation of a wavefront:
+// a wavefront filters its rows and the halo's vertically (92 per row), its
+// output rows horizontally with the index (111), and pays about 600 once. The
+// chip holds 2048 of these wavefronts, two per SIMD, in a round; fewer than half
+// of that (one per SIMD) take 0.6 of a round, and after full rounds 0.35 to 0.5
+// (measured; strips of two wavefronts then pair up on half of the SIMDs). So:
+// the fewest wavefronts that cover the width with strips of 54, 118 or 246
+// outputs (776 planes of 150 x 257: five of one wavefront 184 us, two of four
+// took 516), strips of even height (150 rows as 70 and 70 outputs, not 132 and
+// 8), and short ones where there are few planes (one 1080p RGBA frame: 16 strips
+// of 67 rows 53 us, 45 of 24 took 68). At most 136 rows where the room allows
+// (a lane's sums stay short), and no more strips than the workspace's room.
+// Widths of 65 to 74 columns pay two wavefronts where filtering horizontally
+// first took one, ten of whose lanes loaded twice: 3076 planes of 150 x 65
+// 285 us against 245.
+StripPlan strip_plan(int64_t planes, int h, int w) {
+    constexpr int64_t kSlots = 2048;
+    const int out_w = w - kHalo, out_h = h - kHalo;
+    int room_x, room_y;
+    room(h, w, room_x, room_y);
+    StripPlan best{4, 0, 0};
+    double best_time = 0.0;
+    int64_t best_waves = 0;
+    for (int nw = 4; nw >= 1; nw /= 2) {
+        const int sx = (out_w + 64 * nw - kHalo - 1) / (64 * nw - kHalo);
+        const int64_t fit = static_cast<int64_t>(room_x) * room_y / sx;
+        if (fit < 1) continue;  // (four wavefronts always fit: sx <= room_x)
+        int64_t least = (out_h + 135) / 136, most = (out_h + 7) / 8;
+        if (most > 64 + least) most = 64 + least;
+        if (most > fit) most = fit;
+        if (least > most) least = most;
+        for (int64_t n = least; n <= most; ++n) {
+            const int rows = static_cast<int>((out_h + n - 1) / n);
+            const int64_t waves = planes * sx * nw * ((out_h + rows - 1) / rows);
+            const int64_t full = waves / kSlots, rest = waves % kSlots;
+            double part = rest == 0 ? 0.0 : 1.0;
+            if (rest > 0 && rest <= kSlots / 2) {
+                part = 0.6;
+                if (full > 0) part = rest <= kSlots / 4 ? 0.35 : (nw == 2 ? 0.85 : 0.5);
+            }
+            const double time = (static_cast<double>(full) + part) *
+                                ((rows + kHalo + 3) / 4 * 4 * 92.0 + rows * 111.0 + 600.0);
+            if (best.rows == 0 || time < best_time || (time == best_time && waves < best_waves)) {
+                best = StripPlan{nw, sx, rows};
+                best_time = time;
+                best_waves = waves;
+            }
+            if (waves > 8 * kSlots) break;  // shorter strips only add halo rows
+        }
+    }
+    return best;
+}
+
 template <typename T>
 void launch_strips(int nw, dim3 grid, hipStream_t st, const QualityArgs &a) {
     switch (nw) {
@@ -246,21 +304,11 @@ hipError_t launch_quality(int dtype, const void *pred, const void *truth, int b,
     QualityArgs a;
     a.h = h;
     a.w = w;
-    // As few wavefronts per strip as cover the width (at most four), and
-    // strips of 132 output rows (10 halo rows each) where they still make
-    // several workgroups per CU, else of 66 or 24: the shorter the strip, the
-    // more workgroups for small batches. Their number stays within the
-    // workspace's room (strips of 54 or 118 outputs are used alone in a row).
-    const int nw = w - kHalo <= 64 - kHalo ? 1 : (w - kHalo <= 128 - kHalo ? 2 : 4);
-    a.strips_x = (w - kHalo + 64 * nw - kHalo - 1) / (64 * nw - kHalo);
-    int room_x, room_y;
-    room(h, w, room_x, room_y);
-    const int64_t columns = static_cast<int64_t>(b) * c * a.strips_x;
-    auto rows = [&](int strip) { return (h - kHalo + strip - 1) / strip; };
-    a.strip_rows = 132;
-    if (columns * rows(132) < 2048) a.strip_rows = 66;
-    if (columns * rows(66) < 768 && a.strips_x * rows(24) <= room_x * room_y) a.strip_rows = 24;
-    a.strips_y = rows(a.strip_rows);
+    const StripPlan plan = strip_plan(static_cast<int64_t>(b) * c, h, w);
+    const int nw = plan.nw;
+    a.strips_x = plan.strips_x;
+    a.strip_rows = plan.rows;
+    a.strips_y = (h - kHalo + plan.rows - 1) / plan.rows;
     double e[kWin], sum = 0.0;
     for (int i = 0; i < kWin; ++i) {
         const double r = i - (kWin - 1) / 2;

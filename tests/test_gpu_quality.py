@@ -126,3 +126,25 @@ def test_quality_strip_edges(shape):
     pred = np.clip(truth + rng.normal(0, 0.05, shape), 0, 1).astype(np.float32)
     announce("frame quality strips", shape)
     assert_quality(gpu_quality(pred, truth, "f32", dev), pred, truth, "f32", f"shape {shape}")
+
+
+# Strips of one, two and four wavefronts side by side and above each other.
+@pytest.mark.parametrize("shape", [(3, 4, 150, 74), (3, 4, 150, 129), (2, 1, 290, 134),
+                                   (2, 2, 150, 257), (1, 3, 333, 333), (60, 4, 150, 300),
+                                   (400, 3, 41, 310)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_quality_strip_widths_and_heights(shape, dtype):
+    dev = need_gpu()
+    rng = np.random.default_rng(sum(shape))
+    few = (2,) + shape[1:]  # two different frames, repeated over the batch
+    truth = rng.random(few).astype(np.float32)
+    pred = np.clip(truth + rng.normal(0, 0.05, few), 0, 1).astype(np.float32)
+    which = np.arange(shape[0]) % 2
+    announce("frame quality strips", shape, dtype)
+    p, t = to_dev(pred, dtype, dev), to_dev(truth, dtype, dev)
+    sel = torch.from_numpy(which).to(dev)
+    q = exw.frame_quality(p[sel], t[sel])
+    torch.cuda.synchronize()
+    got = q.cpu().numpy()
+    assert np.array_equal(got, got[which])  # equal frames, equal results
+    assert_quality(got[:2], pred[which[:2]], truth[which[:2]], dtype, f"shape {shape}")

@@ -59,17 +59,21 @@ void launch_at(int i, unsigned long long *out) {
 
 CHILD = r"""
 import ctypes, json, sys
-stand_in, lib, name, args = json.loads(sys.argv[1])
+stand_in, lib, name, calls = json.loads(sys.argv[1])
 s = ctypes.CDLL(stand_in, mode=ctypes.RTLD_GLOBAL)
 fn = getattr(ctypes.CDLL(lib), name)
 conv = {"i": ctypes.c_int32, "p": ctypes.c_void_p, "z": ctypes.c_size_t, "d": ctypes.c_double,
         "f": lambda v: (ctypes.c_float * len(v))(*v)}
-status = fn(*[conv[t](v) for t, v in args])
-out, rec = [], (ctypes.c_ulonglong * 4)()
-for i in range(s.launch_count()):
-    s.launch_at(i, rec)
-    out.append(list(rec))
-print(json.dumps([status, out]))
+results = []
+for args in calls:
+    first = s.launch_count()
+    status = fn(*[conv[t](v) for t, v in args])
+    out, rec = [], (ctypes.c_ulonglong * 4)()
+    for i in range(first, s.launch_count()):
+        s.launch_at(i, rec)
+        out.append(list(rec))
+    results.append([status, out])
+print(json.dumps(results))
 """
 
 # Addresses far apart (1 TB), never read.
@@ -83,8 +87,8 @@ def launches_of(tmp_path_factory):
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-w", str(d / "hip.c"), "-o",
                     str(d / "hip.so")], check=True)
 
-    def run(name, args):
-        job = json.dumps([str(d / "hip.so"), _capi.LIB_PATH, name, args])
+    def run(name, *calls):
+        job = json.dumps([str(d / "hip.so"), _capi.LIB_PATH, name, calls])
         r = subprocess.run([sys.executable, "-c", CHILD, job], capture_output=True, text=True,
                            check=True)
         return json.loads(r.stdout)
@@ -117,7 +121,7 @@ def test_adjoint_of_many_tiny_frames(launches_of, n, recorded):
     512-thread tiles would reach 2^32 work-items."""
     phases = [1.0]
     name = "exw_warp_backward_batched" + ("_recorded" if recorded else "")
-    status, launches = launches_of(name, [
+    [[status, launches]] = launches_of(name, [
         SRC, ("i", 0), ("i", n), ("i", 1), ("i", 1), ("i", 1), MV, ("f", phases), ("i", 1), GOUT,
         GSRC, GMV, WS, ("z", 1 << 40), ("p", 0)])
     assert status == 0
@@ -133,7 +137,7 @@ def test_emd_of_many_planes(launches_of, c, hw, n, dtype):
     if n * c * hw > 1 << 40 or n * c >= 1 << 24:
         pytest.skip("not accepted")
     esize = 2 if dtype else 4
-    status, launches = launches_of("exw_buffer_emd", [
+    [[status, launches]] = launches_of("exw_buffer_emd", [
         ("p", 1 << 42), ("p", 1 << 43), ("i", dtype), ("i", n), ("i", c), ("i", 1), ("i", hw),
         ("d", -1.0), ("d", 1.0), ("i", 64), ("p", 1 << 40), ("p", 1 << 41), ("z", 1 << 40), ("p", 0)])
     assert status == 0
@@ -154,11 +158,28 @@ def covered_planes(hist, planes, plane_bytes):
 @pytest.mark.parametrize("dtype", [0, 2])
 def test_quality_of_many_planes(launches_of, b, c, h, w, dtype):
     esize = 2 if dtype else 4
-    status, launches = launches_of("exw_frame_quality", [
-        ("p", 1 << 43), ("p", 1 << 42), ("i", dtype), ("i", b), ("i", c), ("i", h), ("i", w),
-        ("d", 1.0), ("p", 1 << 40), ("p", 1 << 41), ("z", 1 << 40), ("p", 0)])
+    [[status, launches]] = launches_of("exw_frame_quality", quality_call(b, c, h, w, dtype))
     assert status == 0
     # the strip kernel starts from pred, the fold of the frames from the workspace
     strips = [r for r in launches if r[3] >= 1 << 43]
     per_plane = strips[0][1] // covered_planes(strips, b * c, h * w * esize)
     assert_consecutive(covered(strips, 1 << 43, h * w * esize, per_plane), b * c)
+
+
+def quality_call(b, c, h, w, dtype):
+    return [("p", 1 << 43), ("p", 1 << 42), ("i", dtype), ("i", b), ("i", c), ("i", h), ("i", w),
+            ("d", 1.0), ("p", 1 << 40), ("p", 1 << 41), ("z", 1 << 40), ("p", 0)]
+
+
+def test_quality_strips_fit_the_workspace(launches_of):
+    """One pair of partial sums per strip: the strips of a plane never
+    outnumber the 64 x 66 blocks of positions the workspace is sized by."""
+    shapes = [(b, c, h, w) for b, c in ((1, 1), (3, 4), (700, 3))
+              for h in (11, 19, 76, 77, 150, 270, 1080, 4000)
+              for w in (11, 64, 65, 74, 75, 128, 129, 138, 139, 256, 257, 266, 333, 1000, 1920)]
+    results = launches_of("exw_frame_quality", *[quality_call(*s, 0) for s in shapes])
+    for (b, c, h, w), (status, launches) in zip(shapes, results):
+        assert status == 0
+        strips = [r for r in launches if r[3] >= 1 << 43]
+        room = _capi.lib().exw_frame_quality_workspace_bytes(b, c, h, w) // 16
+        assert 0 < sum(r[1] for r in strips) <= room, (b, c, h, w)
