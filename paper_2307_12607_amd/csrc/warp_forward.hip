@@ -11,13 +11,13 @@
 // wavefronts per 128 x 4 tile (a workgroup, or four consecutive workgroups of
 // one wavefront for twelve 16-bit channels), tiles renumbered per XCD. The
 // motion vector is read once for all K phases; motion, output and mask
-// accesses are coalesced; the taps of neighbouring lanes fall on neighbouring addresses
-// wherever the motion is locally smooth. A segment whose 128 pixels share one
-// integer tap offset per phase takes two pixels per lane (two-element loads
-// and stores plus a lane shift); otherwise each 64-pixel half runs the
-// one-pixel paths: a wavefront whose lanes share one offset loads one aligned
-// element per row and channel plus a lane shift, others load the two
-// horizontal taps of a row in one (unaligned) 8-byte load. Measured HBM
+// accesses are coalesced; the taps of neighbouring lanes fall on neighbouring
+// addresses wherever the motion is locally smooth. A segment whose 128 pixels
+// share one integer tap offset per phase takes two pixels per lane (64 apart or
+// adjacent, see adjacent_pixels; the right taps by a lane shift); otherwise each
+// 64-pixel half runs the one-pixel paths: a wavefront whose lanes share one
+// offset loads one aligned element per row and channel plus a lane shift, others
+// load the two horizontal taps of a row in one (unaligned) load. Measured HBM
 // traffic equals the algorithmic bytes (the L2 serves the overlap between
 // tiles), so the taps are gathered from global memory; an LDS-staged variant
 // and four pixels per lane were both measured slower. No MFMA: this is a
@@ -397,18 +397,13 @@ __device__ __forceinline__ void store_pair(T *p, float a, float b) {
 
 // Two pixels per lane of the wavefront's 128-pixel row segment, taken when
 // every pixel is in the frame and each phase has one integer tap offset for
-// the whole segment. Lane j owns pixels j and j + 64: their left taps are
-// two aligned single-element loads of 64 consecutive columns each, and their
-// right taps are lane j+1's left taps (a DPP shift; lane 63's are lane 0's
-// second one, and one load spread over lanes 0 .. 2C-1). ADJ (the kernels that
-// also form the statistics): lane j owns pixels 2j and 2j + 1, whose taps are
-// columns c, c+1 (one two-element load) and c+2 (lane j+1's first element), and
-// both outputs of a plane are stored at once. ADJ issues half the loads and
-// stores, but an 8-byte or misaligned load takes 16.7 cycles of a CU's texture
-// unit per wavefront where an aligned single one takes 5.2: split, 4 x 4K
-// RGBA f32 three phases 695 -> 665 us, 8 x 1080p 360 -> 346 (one phase 152 ->
-// 149), f16 246 -> 244. With the statistics, twelve 16-bit channels took 94
-// VGPRs instead of 63 that way.
+// the whole segment. Split (ADJ false): lane j owns pixels j and j + 64; their
+// left taps are two aligned single-element loads of 64 consecutive columns
+// each, and their right taps are lane j+1's left taps (a DPP shift; lane 63's
+// are lane 0's second one, and one load spread over lanes 0 .. 2C-1). Adjacent
+// (ADJ): lane j owns pixels 2j and 2j + 1, whose taps are columns c, c+1 (one
+// two-element load) and c+2 (lane j+1's first element), and both outputs of a
+// plane are stored at once.
 // Phases with the offsets of the previous phase reuse its samples. The
 // blend is that of the one-pixel path, term for term. (u0, v0), (u1, v1): the
 // motion of the lane's two pixels; after_first_loads() runs once the first
@@ -523,18 +518,44 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
     return true;  // no invalid pixel: the zeroed counts stay as they are
 }
 
+// Which form of pair_uniform a kernel takes. Adjacent pixels take half the loads
+// and stores, but an 8-byte or misaligned load takes 16.7 cycles of a CU's
+// texture unit per wavefront where an aligned single one takes 5.2. In float32
+// the split form wins (three phases, adjacent against split: 8 x 1080p RGBA
+// 379 us against 360, RGB 297 and 284, 4 x 4K RGBA 746 and 716; 12 channels, two
+// phases 366 and 355). In 16 bits an adjacent pair is one dword, and the split
+// form pays in 2-byte stores: it wins for three and four channels of several
+// phases (recording: RGBA 247 us against 237, two phases 179 and 173, RGB 209 and
+// 200; 4 x 4K 472 and 455; with masks RGBA two phases are even, 239 and 243), and
+// loses elsewhere (8 x 1080p one phase RGBA 99.0 and 100.6, RGB 88.2 and 89.4;
+// 4 x 1080p of 12 channels 125 and 129, two phases 233 and 244).
+// The kernels with statistics keep adjacent pixels, and with them the order of
+// their sums.
+template <typename T, int CT, int KT, bool STATS>
+constexpr bool adjacent_pixels() {
+    return STATS || (sizeof(T) == 2 && (KT == 1 || CT == 1 || CT == 12));
+}
+
 // pair_uniform with the lane's motion loaded here (the kernels without
 // statistics: the loads stay next to their first use).
 template <typename T, int CT, int KT>
 __device__ __forceinline__ bool pair_uniform_load(const FwdArgs<T> &a, const SegPos &g,
                                                   int (&orx)[KT], int (&ory)[KT]) {
+    constexpr bool ADJ = adjacent_pixels<T, CT, KT, false>();
     const int64_t hw = static_cast<int64_t>(a.h) * a.w;
     const float *mu = a.mv + 2 * static_cast<int64_t>(g.in) * hw;
     const uint32_t p = static_cast<uint32_t>(g.y) * static_cast<uint32_t>(a.w) +
-                       static_cast<uint32_t>(g.sx0 + static_cast<int>(threadIdx.x));
-    const float u0 = *at(mu, p), u1 = *at(mu, p + kSegW);
-    const float v0 = *at(mu + hw, p), v1 = *at(mu + hw, p + kSegW);
-    return pair_uniform<false, T, CT, KT>(a, g, u0, u1, v0, v1, orx, ory, [] {});
+                       static_cast<uint32_t>(g.sx0 + static_cast<int>(ADJ ? 2 * threadIdx.x
+                                                                          : threadIdx.x));
+    float u0, u1, v0, v1;
+    if constexpr (ADJ) {
+        load_pair(at(mu, p), u0, u1);
+        load_pair(at(mu + hw, p), v0, v1);
+    } else {
+        u0 = *at(mu, p); u1 = *at(mu, p + kSegW);
+        v0 = *at(mu + hw, p); v1 = *at(mu + hw, p + kSegW);
+    }
+    return pair_uniform<ADJ, T, CT, KT>(a, g, u0, u1, v0, v1, orx, ory, [] {});
 }
 
 // Footprint records of the wavefront's two 64-pixel segments after the
@@ -724,7 +745,8 @@ __global__ __launch_bounds__(kThreads) void warp_forward_kernel(FwdArgs<T> a) {
             int rx[KT], ry[KT];
             // (the sums are formed while the first gathers are in flight)
             if (a.frame_32bit && g.y < a.h && g.sx0 + kSegPair <= a.w &&
-                pair_uniform<true, T, CT, KT>(a, g, u0, u1, v0, v1, rx, ry, sums)) {
+                pair_uniform<adjacent_pixels<T, CT, KT, true>(), T, CT, KT>(
+                    a, g, u0, u1, v0, v1, rx, ry, sums)) {
                 record_pair<T, KT>(a, g, rx, ry);
                 done = true;
             }
