@@ -130,7 +130,9 @@ size_t exw_warp_backward_workspace_bytes(exw_dtype dtype, int32_t n, int32_t c, 
  * Adjoint of exw_warp_forward_batched: given grad_out = dL/d out, writes
  *   grad_src = dL/d src  = sum over k of the transpose of the bilinear gather
  *              (each valid output pixel sends weight * grad_out to its four
- *              taps), accumulated in float32 and rounded once into dtype;
+ *              taps), accumulated in float64 and rounded to float32, then to
+ *              dtype (channel counts other than 1, 2, 3, 4 and 12, and taps
+ *              more than 128 px away: accumulated in float32);
  *   grad_mv  = dL/d mv   = -s * sum_c grad_out[c] * d out[c]/d(sx, sy),
  *              summed over k, 0 at invalid pixels; at a floor kink the
  *              derivative is the one-sided one of the cell the pixel samples.
@@ -142,12 +144,14 @@ size_t exw_warp_backward_workspace_bytes(exw_dtype dtype, int32_t n, int32_t c, 
  *           exw_warp_backward_workspace_bytes(...) bytes, 256-byte aligned;
  *           its contents are scratch. May be NULL when grad_src is NULL.
  * The image gradient is formed by gathering, per tile of the image, the
- * contributions of the output pixels whose taps land there (LDS
+ * contributions of the output pixels whose taps land there (float64 LDS
  * accumulation, plain stores); output segments whose taps lie more than 128
- * px away fall back to float32 atomics. The summation order is fixed except
- * where atomics are used (taps at motion boundaries of frames with 1, 2, 4
- * or 12 channels are added with LDS atomics, far segments with global ones),
- * so the last bits of grad_src can differ from run to run.
+ * px away, and channel counts other than 1, 2, 3, 4 and 12, use float32
+ * atomics. The order of the additions is not fixed. The contributions are
+ * float32 values, so their float64 sums seldom round at all, and a result
+ * differs from run to run only where two orders of them straddle a float32
+ * rounding boundary; sums of the float32 atomics can differ in their last
+ * bits. grad_mv is the same in every run.
  */
 exw_status exw_warp_backward_batched(const void *src, exw_dtype dtype, int32_t n, int32_t c,
                                      int32_t h, int32_t w, const float *mv, const float *phases,

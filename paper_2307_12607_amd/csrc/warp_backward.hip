@@ -318,7 +318,8 @@ struct SegLoad {
 // phase 634 -> 324, RGBA three phases 3470 -> 690; a zooming camera, RGBA three
 // phases 712 -> 456.) The sums of a cell land in any order; rounded from
 // float64, they differ from run to run only where two orders straddle a
-// float32 rounding boundary.
+// float32 rounding boundary (none of 66 to 177 million elements did in six runs
+// of each of five training batches).
 //
 // Work list: the segments whose boxes reach the tile (only rows and columns
 // within the per-frame reach can), plus the tile's own segments ("home"),

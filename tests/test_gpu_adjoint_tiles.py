@@ -71,3 +71,47 @@ def test_more_frames_than_one_launch_of_tiles_holds():
                               [1.0], g)
     torch.cuda.synchronize()
     assert torch.equal(gs, g[:, 0])
+
+
+@pytest.mark.parametrize("c", [1, 2, 3, 4, 12])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+def test_sums_are_float64_and_rounded_at_the_end(c, dtype):
+    """Motion in eighths and whole upstream gradients: every weight, product
+    and float64 sum is exact, whatever the order of the additions, also where
+    hundreds of pixels meet in one cell (where float32 sums would round). The
+    image gradient is then the exact sum rounded to float32 and to the storage
+    type, in every run. (The segments from column 256 on of the converging rows
+    lie more than 128 pixels from that cell: their contributions are float32
+    atomics, and the cells they reach are only bounded.)"""
+    dev = need_gpu()
+    rng = np.random.default_rng(c)
+    h, w, phases = 40, 300, [0.5, 1.0]
+    mv = mixed_motion(rng, h, w)
+    mv[:, :, h // 3:2 * h // 3] = rng.integers(-40, 41, mv[:, :, h // 3:2 * h // 3].shape) / 8
+    # storable in every type: 8 significant bits
+    g = (rng.integers(-255, 256, (1, 2, c, h, w)) * 4096.0 + 0.0).astype(np.float32)
+    g[:, :, :, ::2] /= 4096.0
+    if dtype == "f16":
+        g /= 64.0  # within its range
+    src = rng.random((1, c, h, w), dtype=np.float32)
+    exact, _ = warp_oracle.backward(src, mv, phases, g)
+    want = torch.from_numpy(exact).to(torch.float32).to({"f32": torch.float32, "f16": torch.float16,
+                                                         "bf16": torch.bfloat16}[dtype])
+    far = np.zeros_like(g)
+    far[..., 2 * (h // 3):, 256:] = 1.0
+    by_atomics = torch.from_numpy(warp_oracle.backward(src, mv, phases, far)[0] != 0)
+    # at most 512 additions to a cell, each rounding by 2^-24 of the magnitudes
+    bound = torch.from_numpy(2.0 ** -15 * warp_oracle.backward(src, mv, phases, np.abs(g))[0]
+                             + (0.0 if dtype == "f32" else half_ulp(exact, dtype)))
+    # (sums beyond float16's range are infinite)
+    bounded = by_atomics & (torch.from_numpy(np.abs(exact)) + bound < torch.finfo(want.dtype).max)
+    assert bounded.any() and by_atomics.float().mean() < 0.2
+    announce("exact sums", c, dtype)
+    args = (to_dev(src, dtype, dev), torch.from_numpy(mv).to(dev), phases, to_dev(g, dtype, dev))
+    for _ in range(3):
+        gs, _ = exw.warp_backward(*args)
+        torch.cuda.synchronize()
+        gs = gs.cpu()
+        assert torch.equal(gs[~by_atomics], want[~by_atomics])
+        err = (gs.double() - torch.from_numpy(exact)).abs()
+        assert (err[bounded] <= bound[bounded]).all()
