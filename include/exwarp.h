@@ -366,8 +366,10 @@ size_t exw_frame_quality_workspace_bytes(int32_t b, int32_t c, int32_t h, int32_
  *   peak:        the value range of the frames (1.0 for unit-range frames;
  *                the paper's 255 for 8-bit frames), finite and > 0.
  * All window sums, the SSIM index and the sums are float64; the order of
- * every sum is fixed, so results are reproducible bit for bit. B = 0 does
- * nothing; H or W below 11 is EXW_ERROR_INVALID_VALUE.
+ * every sum is fixed by the shape, so results are reproducible bit for bit.
+ * How a frame is divided among workgroups depends on B too, so the last bits
+ * of a frame's results can differ between a batch and the frame alone. B = 0
+ * does nothing; H or W below 11 is EXW_ERROR_INVALID_VALUE.
  */
 exw_status exw_frame_quality(const void *pred, const void *truth, exw_dtype dtype, int32_t b,
                              int32_t c, int32_t h, int32_t w, double peak, double *quality,

@@ -15,8 +15,8 @@
 // Four finished rows at a time go through LDS, where each lane takes four
 // adjacent output columns of one row: 14 columns are read for 4 outputs, so
 // LDS moves 14 / 4 values per output and sum instead of 11. The squared errors
-// for the MSE are summed on the way. Partials are folded per frame in a fixed
-// order, so the results are reproducible bit for bit.
+// for the MSE are summed on the way. Partials are folded per frame in an
+// order fixed by the batch's shape, so the results are reproducible bit for bit.
 //
 // Bound: the float64 vector ALU, which issues at the rate of unpacked float32
 // (float32 sums would lose the low digits of E[x^2] - E[x]^2). Operations per

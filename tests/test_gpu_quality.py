@@ -148,3 +148,20 @@ def test_quality_strip_widths_and_heights(shape, dtype):
     got = q.cpu().numpy()
     assert np.array_equal(got, got[which])  # equal frames, equal results
     assert_quality(got[:2], pred[which[:2]], truth[which[:2]], dtype, f"shape {shape}")
+
+
+@pytest.mark.parametrize("shape", [(16, 4, 150, 257), (40, 3, 270, 480), (6, 1, 700, 70)])
+def test_quality_of_a_frame_alone_and_in_a_batch(shape):
+    """The strips, and with them the order of the sums, depend on the batch.
+    A sum is a chain of at most 180 additions of terms of one sign (MSE) or of
+    magnitude at most 1 (SSIM), each off by 2^-53: 2^-44 bounds two of them."""
+    dev = need_gpu()
+    rng = np.random.default_rng(sum(shape))
+    truth = to_dev(rng.random(shape).astype(np.float32), "f32", dev)
+    pred = to_dev(rng.random(shape).astype(np.float32), "f32", dev)
+    announce("frame quality alone and in a batch", shape)
+    batch = exw.frame_quality(pred, truth).cpu().numpy()
+    for i in (0, shape[0] - 1):
+        alone = exw.frame_quality(pred[i:i + 1], truth[i:i + 1]).cpu().numpy()[0]
+        assert abs(alone[0] - batch[i, 0]) <= 2.0 ** -44 * batch[i, 0]
+        assert abs(alone[2] - batch[i, 2]) <= 2.0 ** -44
