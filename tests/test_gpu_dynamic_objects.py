@@ -155,3 +155,20 @@ def test_tile_edges(h, w):
         np.array([1, 2, 16, 128, 255], np.uint8), (5, h, w))
     announce("dynamic objects tiles", h, w)
     check(st, f"tiles {h} x {w}", dev)
+
+
+def test_frame_at_the_size_limit_across_tile_borders():
+    """The same frame with the squares shifted 24 pixels to the left, so that
+    each of them crosses a column border of the 64 x 32 tiles as well as a row
+    border: 513 columns of squares (the first and the last cut in half)."""
+    dev = need_gpu()
+    side = 1 << 15
+    announce("dynamic objects at the size limit, shifted", side, side)
+    i = torch.arange(side, device=dev)
+    st = (((i % 64) < 48)[:, None] & (((i + 24) % 64) < 48)[None, :]).to(torch.uint8)[None]
+    for conn in (4, 8):
+        got = exw.dynamic_objects(st, conn)
+        torch.cuda.synchronize()
+        assert got.cpu().tolist() == [(side // 64) * (side // 64 + 1)], (conn, got)
+    del st
+    torch.cuda.empty_cache()
