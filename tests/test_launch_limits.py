@@ -183,3 +183,17 @@ def test_quality_strips_fit_the_workspace(launches_of):
         strips = [r for r in launches if r[3] >= 1 << 43]
         room = _capi.lib().exw_frame_quality_workspace_bytes(b, c, h, w) // 16
         assert 0 < sum(r[1] for r in strips) <= room, (b, c, h, w)
+
+
+@pytest.mark.parametrize("n,h,w", [(1, 1080, 1920), (1 << 23, 1, 1), ((1 << 24) + 7, 3, 5), (1, 1 << 28, 1),
+                                   (1, 1 << 30, 1), (3, (1 << 28) + 40, 2)])
+def test_dynamic_objects_of_many_tiles(launches_of, n, h, w):
+    [[status, launches]] = launches_of("exw_dynamic_objects", [
+        ("p", 1 << 42), ("i", n), ("i", h), ("i", w), ("i", 8), ("p", 1 << 40), ("p", 1 << 43),
+        ("z", 1 << 45), ("p", 0)])
+    assert status == 0
+    tiles = n * -(-h // 32) * -(-w // 64)
+    passes = [r for r in launches if r[3] == 1 << 42]  # both passes start from the stencil
+    kernels = list(dict.fromkeys(r[0] for r in passes))
+    grids = [sum(r[1] for r in passes if r[0] == k) for k in kernels]
+    assert grids == [tiles, -(-tiles // 2)]  # one tile, and two tiles, per workgroup
