@@ -193,7 +193,8 @@ struct PTaps {
     bool valid;
 };
 
-template <typename T, int CT>
+// TILES: called by the tile kernel (else by the motion-only kernel).
+template <typename T, int CT, bool TILES>
 __device__ __forceinline__ void motion_grad_phase(const T *const *iplane, int w, const PTaps &t,
                                                   const float *g, float s, float &gu, float &gv) {
     const int xl = min(t.ax.i0, w - 2);
@@ -212,15 +213,27 @@ __device__ __forceinline__ void motion_grad_phase(const T *const *iplane, int w,
         }
     };
     // Twelve 16-bit channels: every channel's samples are loaded, under one
-    // column test, before any is used (4 x 1440p bf16: 940 -> 864 us; with
-    // the column test repeated per channel the gain was lost), and they wait
-    // as loaded, two to a register: widened at the load they took 99 VGPRs
-    // instead of 73, a third workgroup per CU. Elsewhere each channel's loads
-    // come with its use: the batched form was 3-15 % slower for four 16-bit
-    // channels and for twelve float32 ones.
+    // column test, before any is used. In the tile kernel they wait as loaded,
+    // two to a register (widened at the load they took 99 VGPRs instead of 73, a
+    // third workgroup per CU: 4 x 1440p bf16 537 -> 507 us); in the motion-only
+    // kernel, where registers are no limit, widened (2 x 720p bf16 under i.i.d.
+    // motion 69 us, 80 as loaded). Elsewhere each channel's loads come with its
+    // use: the batched form was 3-15 % slower for four 16-bit channels and for
+    // twelve float32 ones.
     constexpr bool batch = CT == 12 && sizeof(T) == 2;
-    uint32_t p0[CT], p1[CT];  // the batch: left tap in the low half
-    if constexpr (batch) {
+    uint32_t p0[CT], p1[CT];  // the batch of the tile kernel: left tap in the low half
+    if constexpr (batch && !TILES) {
+        if (w >= 2) {  // wave-uniform
+#pragma unroll
+            for (int ch = 0; ch < CT; ++ch) {
+                load_pair(at(iplane[ch], o0), a0[ch], b0[ch]);
+                load_pair(at(iplane[ch], o1), a1[ch], b1[ch]);
+            }
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < CT; ++ch) load_channel(ch);
+        }
+    } else if constexpr (batch) {
         if (w >= 2) {  // wave-uniform
 #pragma unroll
             for (int ch = 0; ch < CT; ++ch) {
@@ -242,12 +255,12 @@ __device__ __forceinline__ void motion_grad_phase(const T *const *iplane, int w,
     float su = 0.0f, sv = 0.0f;
 #pragma unroll
     for (int ch = 0; ch < CT; ++ch) {
-        if constexpr (batch) {
+        if constexpr (batch && TILES) {
             a0[ch] = half_bits_to_f32(p0[ch], static_cast<T *>(nullptr));
             b0[ch] = half_bits_to_f32(p0[ch] >> 16, static_cast<T *>(nullptr));
             a1[ch] = half_bits_to_f32(p1[ch], static_cast<T *>(nullptr));
             b1[ch] = half_bits_to_f32(p1[ch] >> 16, static_cast<T *>(nullptr));
-        } else {
+        } else if constexpr (!batch) {
             load_channel(ch);
         }
         const float i00 = last ? b0[ch] : a0[ch], i01 = b0[ch];
@@ -640,7 +653,7 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
             if (per_channel) {
 #pragma unroll
                 for (int k = 0; k < KT; ++k)
-                    if (t[k].valid) motion_grad_phase<T, CT>(iplane, w, t[k], g[k], a.s[k], gu, gv);
+                    if (t[k].valid) motion_grad_phase<T, CT, true>(iplane, w, t[k], g[k], a.s[k], gu, gv);
             }
             if (inx) {
                 float *gm = a.gmv + 2 * static_cast<int64_t>(in) * hw;
@@ -838,7 +851,7 @@ __global__ __launch_bounds__(kThreads) void motion_grad_kernel(BwdArgs<T> a) {
         float g[CT];
 #pragma unroll
         for (int ch = 0; ch < CT; ++ch) g[ch] = to_f32(gp[ch * hw]);
-        motion_grad_phase<T, CT>(iplane, w, t, g, a.s[k], gu, gv);
+        motion_grad_phase<T, CT, false>(iplane, w, t, g, a.s[k], gu, gv);
     }
     a.gmv[(2 * static_cast<int64_t>(in)) * hw + p] = gu;
     a.gmv[(2 * static_cast<int64_t>(in) + 1) * hw + p] = gv;
