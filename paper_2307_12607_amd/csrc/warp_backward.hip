@@ -417,8 +417,13 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
     // (the first boxes are on their way while the tile is cleared)
     Box bx = box_of(wave * kSegW + lane);
     if (threadIdx.x == 0) list_len = 0;
-    for (int i = threadIdx.x; i < CT * Tile::cells / 2; i += NW * kSegW)
-        reinterpret_cast<f64x2 *>(acc)[i] = f64x2{0.0, 0.0};
+    // Cells of the tile's rows in the frame: only these are cleared and stored
+    // (additions below them, of clamped taps of weight 0, are never read).
+    const int live = min(TH, h - ty0) * TW;
+#pragma unroll
+    for (int ch = 0; ch < CT; ++ch)
+        for (int i = threadIdx.x; i < live / 2; i += NW * kSegW)
+            reinterpret_cast<f64x2 *>(acc + ch * Tile::cells)[i] = f64x2{0.0, 0.0};
     __syncthreads();
 
     // The segments to replay, listed by all wavefronts together as
@@ -727,9 +732,9 @@ __global__ __launch_bounds__((TileShape<T, CT, KT>::waves * kSegW)) void adjoint
     // frames that also receive far-segment atomics go through the float32
     // accumulator instead.
     const bool to_accum = fi.has_far && a.accum32 != nullptr;
-    for (int c = threadIdx.x; c < Tile::cells; c += NW * kSegW) {
+    for (int c = threadIdx.x; c < live; c += NW * kSegW) {
         const int X = tx0 + c % TW, Y = ty0 + c / TW;
-        if (X >= w || Y >= h) continue;
+        if (X >= w) continue;
         const uint32_t o = static_cast<uint32_t>(Y) * static_cast<uint32_t>(w) + X;
         const int64_t frame = static_cast<int64_t>(in) * CT * hw;
 #pragma unroll
