@@ -6,14 +6,12 @@
 // marked pixels are joined when they share an edge (4-connectivity) or an
 // edge or a corner (8-connectivity).
 //
-// Pass 1, one workgroup per 64 x 32 tile: a thread loads four adjacent pixels
+// Pass 1, one workgroup per 64 x 32 tile: a thread loads eight adjacent pixels
 // and turns them into bits, a row of the tile is a 64-bit mask, and each pixel's
 // run of marked pixels, and where two rows touch, are bit operations. Union-find
 // over the runs in LDS: a run's label sits at its first pixel, and links are
 // made once per stretch where two rows touch, all rows at once (each thread
-// those of its four columns: with eight, one frame of 270 x 480 in one-pixel
-// stripes took 18.4 us instead of 14.0, a checkerboard 43.8 instead of 26.6;
-// sparse masks take the same). Labels are in-tile indices; a union links the
+// those of its eight columns). Labels are in-tile indices; a union links the
 // larger root under the smaller with an LDS atomicMin and retries from the old
 // parent when another lane linked it first, so every label points to a smaller
 // or equal index and every find ends. Only the labels that pass 2 can reach are
@@ -33,7 +31,11 @@
 // 20 % / 60 % / 90 % random mask 354 / 574 / 488, now 255 / 285 / 229; fully
 // marked 342, now 193; one 1080p frame with a rectangle 23, now 17. One
 // wavefront per tile, without barriers, was slower where pixels are marked (46
-// against 17 us on that frame: the rows' links one after the other).
+// against 17 us on that frame: the rows' links one after the other); 512 threads
+// of four columns each too, where the marked pixels form solid objects (4 x
+// 1440p with rectangles 35.7 against 31.2 us). Those would suit one-pixel
+// structures in small frames: one frame of 270 x 480 in one-pixel stripes takes
+// 18.3 us, 14.4 with them and 14.2 before; a checkerboard 43, 26 and 39.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -43,7 +45,7 @@ namespace exw {
 namespace {
 
 constexpr int kCcW = 64, kCcH = 32;             // tile (pixels)
-constexpr int kCcThreads = kCcW * kCcH / 4;      // pass 1: four adjacent pixels per thread
+constexpr int kCcThreads = kCcW * kCcH / 8;      // pass 1: eight adjacent pixels per thread
 constexpr int kBorderTiles = 2;                  // pass 2: tiles per workgroup, two wavefronts each
 constexpr int kBorderThreads = 128 * kBorderTiles;
 
@@ -110,7 +112,7 @@ __device__ __forceinline__ int run_start(uint64_t row, int c) {
     return gaps ? 64 - __clzll(static_cast<long long>(gaps)) : 0;
 }
 
-typedef uint32_t u32_b __attribute__((aligned(1)));
+typedef uint64_t u64_u __attribute__((aligned(1)));
 
 __global__ __launch_bounds__(kCcThreads) void cc_tile_kernel(CcArgs a) {
     __shared__ int lab[kCcW * kCcH];
@@ -121,29 +123,27 @@ __global__ __launch_bounds__(kCcThreads) void cc_tile_kernel(CcArgs a) {
     const int tile = job - frame * a.tiles_per_frame;
     const int x0 = (tile % a.tiles_x) * kCcW, y0 = (tile / a.tiles_x) * kCcH;
     const int64_t hw = static_cast<int64_t>(a.h) * a.w;
-    const int r = threadIdx.x / 16, c0 = threadIdx.x % 16 * 4;  // row, first of four columns
-    // The thread's four pixels as four bits.
+    const int r = threadIdx.x / 8, c0 = threadIdx.x % 8 * 8;  // row, first of eight columns
+    // The thread's eight pixels as eight bits.
     uint32_t bits = 0;
     if (y0 + r < a.h) {
         const uint8_t *st = a.stencil + frame * hw + static_cast<int64_t>(y0 + r) * a.w + x0 + c0;
-        if (x0 + c0 + 4 <= a.w) {
-            uint32_t v = *reinterpret_cast<const u32_b *>(st);
+        if (x0 + c0 + 8 <= a.w) {
+            uint64_t v = *reinterpret_cast<const u64_u *>(st);
             v |= v >> 4;
             v |= v >> 2;
             v |= v >> 1;
-            // bit 0 of byte i to bit 28 + i (no two terms of the product meet)
-            bits = ((v & 0x01010101u) * 0x10204080u) >> 28;
+            // bit 0 of byte i to bit 56 + i (no two terms of the product meet)
+            bits = static_cast<uint32_t>(((v & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
         } else {
-            for (int i = 0; x0 + c0 + i < a.w && i < 4; ++i) bits |= (st[i] != 0 ? 1u : 0u) << i;
+            for (int i = 0; x0 + c0 + i < a.w && i < 8; ++i) bits |= (st[i] != 0 ? 1u : 0u) << i;
         }
     }
-    const uint32_t pair = bits | (__shfl_xor(bits, 1) << 4);  // an even thread's byte
-    if (threadIdx.x % 2 == 0)
-        reinterpret_cast<uint8_t *>(rows)[threadIdx.x / 2] = static_cast<uint8_t>(pair);
+    reinterpret_cast<uint8_t *>(rows)[threadIdx.x] = static_cast<uint8_t>(bits);
     if (threadIdx.x == 0) rows[kCcH] = 0;
     if (!__syncthreads_or(bits != 0)) return;  // no marked pixel in the tile
     const uint64_t up = rows[r], dn = rows[r + 1];
-    const uint64_t mine = uint64_t(0xf) << c0;
+    const uint64_t mine = uint64_t(0xff) << c0;
     // a run's label at its first pixel
     const uint64_t starts = up & ~(up << 1) & mine;
     for (uint64_t m = starts; m; m &= m - 1) {
