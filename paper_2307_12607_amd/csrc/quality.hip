@@ -114,13 +114,14 @@ __global__ __launch_bounds__(64 * NW, 2) void ssim_strip_kernel(QualityArgs a) {
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) { cx[q] = nx[q]; cy[q] = ny[q]; }
             load(r0 + kBatch);
+            double batch_sq = 0.0;  // (fewer additions to the long sum)
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) {
                 const int s = bt * kBatch + q;
                 const double x = to_f32(cx[q]), y = to_f32(cy[q]);
                 if (r0 + q < own_rows && own_col) {
                     const double d = x - y;
-                    sq_sum = fma(d, d, sq_sum);
+                    batch_sq = fma(d, d, batch_sq);
                 }
                 const double v[4] = {x, y, fma(x, x, y * y), x * y};
                 // input row r feeds output rows r - t, t = 0 .. 10, kept in
@@ -138,6 +139,7 @@ __global__ __launch_bounds__(64 * NW, 2) void ssim_strip_kernel(QualityArgs a) {
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            sq_sum += batch_sq;
             __syncthreads();
             const int r_out = r0 + grow - kHalo;  // this lane's output row
             if (r_out >= 0 && r_out < rows_out && cols_out > 0) {

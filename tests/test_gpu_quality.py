@@ -165,3 +165,15 @@ def test_quality_of_a_frame_alone_and_in_a_batch(shape):
         alone = exw.frame_quality(pred[i:i + 1], truth[i:i + 1]).cpu().numpy()[0]
         assert abs(alone[0] - batch[i, 0]) <= 2.0 ** -44 * batch[i, 0]
         assert abs(alone[2] - batch[i, 2]) <= 2.0 ** -44
+
+
+def test_mse_adds_four_rows_before_the_long_sum():
+    """Squared errors of 48 bits, 100 rows in one strip: four of them add up
+    exactly, and so do 25 such sums (multiples of 2^-46 below 2^7), while
+    adding them one by one rounds from the 33rd row on."""
+    dev = need_gpu()
+    d = 1.0 - 2.0 ** -24
+    x = torch.full((3000, 1, 100, 64), d, device=dev)
+    announce("frame quality long sums")
+    q = exw.frame_quality(x, torch.zeros_like(x)).cpu().numpy()
+    assert (q[:, 0] == d * d).all()
