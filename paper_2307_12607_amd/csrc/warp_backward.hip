@@ -286,7 +286,7 @@ __device__ __forceinline__ float shift_up1(float v) {
 // 128 x 16, 1.9 at 128 x 12 on pans below a pixel per phase), but the kernel is
 // paid in wavefronts in flight. Four channels, three phases: 80 VGPRs allow 24
 // wavefronts per CU, so three workgroups of 8 must fit the 160 KB of LDS: 12
-// rows (8 x 1080p f32 472 us, f16 439; 16 rows, two workgroups: 506 and 511;
+// rows (8 x 1080p f32 472 us, f16 431; 16 rows, two workgroups: 506 and 511;
 // 8 rows in 4 wavefronts: 511 and 514). Twelve channels, one phase: in 16 bits
 // 73 VGPRs, so three workgroups of 4 rows fit (4 x 1440p bf16 507 us; 5 rows
 // 575, 6 rows 545; i.i.d. motion pays for the smaller tile, 961 us against
@@ -326,10 +326,10 @@ struct SegLoad {
 // need no turns, and a segment that reaches the tile is replayed by one
 // wavefront only. (Before: one wavefront per 128 x 3 tile with float32 cells,
 // 2.8 replays per segment and turns for lanes that share a cell; 8 x 1080p
-// RGBA three phases f32 611 -> 472 us, f16 498 -> 439, 4 x 4K f16 841 -> 760,
-// 4 x 1440p 12-channel bf16 675 -> 507; under i.i.d. motion 8 x 1080p RGB one
-// phase 634 -> 324, RGBA three phases 3470 -> 690; a zooming camera, RGBA three
-// phases 712 -> 456.) The sums of a cell land in any order; rounded from
+// RGBA three phases f32 611 -> 476 us, f16 489 -> 431, 4 x 4K f16 834 -> 762,
+// 4 x 1440p 12-channel bf16 681 -> 509; under i.i.d. motion 8 x 1080p RGB one
+// phase 632 -> 329, RGBA three phases 3475 -> 688; a zooming camera, RGBA three
+// phases 724 -> 462; but without any motion, RGBA f16, 4 x 4K 520 -> 540.) The sums of a cell land in any order; rounded from
 // float64, they differ from run to run only where two orders straddle a
 // float32 rounding boundary (none of 66 to 177 million elements did in six runs
 // of each of five training batches).

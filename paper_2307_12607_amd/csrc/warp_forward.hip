@@ -523,12 +523,15 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
 // texture unit per wavefront where an aligned single one takes 5.2. In float32
 // the split form wins (three phases, adjacent against split: 8 x 1080p RGBA
 // 379 us against 360, RGB 297 and 284, 4 x 4K RGBA 746 and 716; 12 channels, two
-// phases 366 and 355). In 16 bits an adjacent pair is one dword, and the split
-// form pays in 2-byte stores: it wins for three and four channels of several
-// phases (recording: RGBA 247 us against 237, two phases 179 and 173, RGB 209 and
-// 200; 4 x 4K 472 and 455; with masks RGBA two phases are even, 239 and 243), and
-// loses elsewhere (8 x 1080p one phase RGBA 99.0 and 100.6, RGB 88.2 and 89.4;
-// 4 x 1080p of 12 channels 125 and 129, two phases 233 and 244).
+// phases 366 and 355). In 16 bits an adjacent pair is one dword, aligned where
+// the tap offset is even, and the split form pays in 2-byte stores. For three and
+// four channels of several phases it wins at odd offsets and loses less at even
+// ones (recording, 8 x 1080p RGBA f16, three phases, by the pan: (0.3, 2.8) 246
+// us and 216, (3.3, -1.7) 229 and 217, (1, -0.7) 169 and 158; (2.2, -2.7) 215 and
+// 217, (6.1, 4.2) 206 and 216, none 143 and 144; 8 x 4K of the synthetic scenes 781
+// and 785, with masks 762 and 780). It loses elsewhere: 8 x 1080p one phase RGBA
+// 99.0 and 100.6, RGB 88.2 and 89.4; 4 x 1080p of 12 channels 125 and 129, two
+// phases 233 and 244.
 // The kernels with statistics keep adjacent pixels, and with them the order of
 // their sums.
 template <typename T, int CT, int KT, bool STATS>
