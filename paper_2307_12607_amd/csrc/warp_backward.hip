@@ -214,7 +214,7 @@ __device__ __forceinline__ void motion_grad_phase(const T *const *iplane, int w,
     };
     // Twelve 16-bit channels: every channel's samples are loaded, under one
     // column test, before any is used. In the tile kernel they wait as loaded,
-    // two to a register (widened at the load they took 99 VGPRs instead of 73, a
+    // two to a register (widened at the load they took 99 VGPRs instead of 76, a
     // third workgroup per CU: 4 x 1440p bf16 537 -> 507 us); in the motion-only
     // kernel, where registers are no limit, widened (2 x 720p bf16 under i.i.d.
     // motion 69 us, 80 as loaded). Elsewhere each channel's loads come with its
@@ -288,9 +288,9 @@ __device__ __forceinline__ float shift_up1(float v) {
 // wavefronts per CU, so three workgroups of 8 must fit the 160 KB of LDS: 12
 // rows (8 x 1080p f32 472 us, f16 431; 16 rows, two workgroups: 506 and 511;
 // 8 rows in 4 wavefronts: 511 and 514). Twelve channels, one phase: in 16 bits
-// 73 VGPRs, so three workgroups of 4 rows fit (4 x 1440p bf16 507 us; 5 rows
+// 76 VGPRs, so three workgroups of 4 rows fit (4 x 1440p bf16 507 us; 5 rows
 // 575, 6 rows 545; i.i.d. motion pays for the smaller tile, 961 us against
-// 920); in float32 105, so two of 6 rows. Two phases: 6 rows (2 x 1440p bf16
+// 920); in float32 107, so two of 6 rows. Two phases: 6 rows (2 x 1440p bf16
 // 416 us, 4 rows 452). From three on, their registers leave room for 4
 // wavefronts per workgroup (2 x 1440p bf16: three phases, 4 rows 650 us, 6
 // rows 809, 6 rows in 8 wavefronts 888; four phases, 6 rows 1142, 4 rows
@@ -329,10 +329,10 @@ struct SegLoad {
 // RGBA three phases f32 611 -> 476 us, f16 489 -> 431, 4 x 4K f16 834 -> 762,
 // 4 x 1440p 12-channel bf16 681 -> 509; under i.i.d. motion 8 x 1080p RGB one
 // phase 632 -> 329, RGBA three phases 3475 -> 688; a zooming camera, RGBA three
-// phases 724 -> 462; but without any motion, RGBA f16, 4 x 4K 520 -> 540.) The sums of a cell land in any order; rounded from
-// float64, they differ from run to run only where two orders straddle a
-// float32 rounding boundary (none of 66 to 177 million elements did in six runs
-// of each of five training batches).
+// phases 724 -> 462; but without any motion, RGBA f16, 4 x 4K 520 -> 540.) The
+// sums of a cell land in any order; rounded from float64, they differ from run
+// to run only where two orders straddle a float32 rounding boundary (none of 66
+// to 177 million elements did in six runs of each of five training batches).
 //
 // Work list: the segments whose boxes reach the tile (only rows and columns
 // within the per-frame reach can), plus the tile's own segments ("home"),
@@ -348,7 +348,7 @@ struct SegLoad {
 // samples of their motion gradient are aligned loads shared by the phases
 // whose offsets agree. Other segments add each lane's four taps.
 //
-// What bounds it: the vector ALU issues 62 % of the cycles (f16: 75 %) and the
+// What bounds it: the vector ALU issues 64 % of the cycles (f16: 77 %) and the
 // LDS additions 65 %, and neither covers the other at five to six wavefronts per SIMD;
 // HBM traffic is 1.23x the algorithmic bytes (2.1x before). Measured and left
 // out: lane 63's taps gathered into one addition (DPP moves cost more than
