@@ -528,7 +528,7 @@ __device__ __forceinline__ bool pair_uniform(const FwdArgs<T> &a, const SegPos &
 // four channels of several phases it wins at odd offsets and loses less at even
 // ones (recording, 8 x 1080p RGBA f16, three phases, by the pan: (0.3, 2.8) 246
 // us and 216, (3.3, -1.7) 229 and 217, (1, -0.7) 169 and 158; (2.2, -2.7) 215 and
-// 217, (6.1, 4.2) 206 and 216, none 143 and 144; 8 x 4K of the synthetic scenes 781
+// 217, (6.1, 4.2) 206 and 216, none 143 and 144; 8 x 4K with moving rectangles 781
 // and 785, with masks 762 and 780). It loses elsewhere: 8 x 1080p one phase RGBA
 // 99.0 and 100.6, RGB 88.2 and 89.4; 4 x 1080p of 12 channels 125 and 129, two
 // phases 233 and 244.
